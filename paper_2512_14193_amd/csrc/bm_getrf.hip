@@ -3,8 +3,10 @@
 // Used for U33 = -M31 M13 - M32 M23 (Theorem thm:LU) and, as the comparator, for
 // the 2N x 2N ordinary matrix.  Per panel of jb <= 64 columns starting at column j:
 //
-//  1. panel_kernel (P workgroups, all resident at once): the (n - j) x jb panel
-//     is held in LDS for the whole panel, 64 or 128 consecutive rows per
+//  1. the panel factorisation.  Up to 2048 rows: panel_stream_kernel
+//     (bm_panel_stream.h), each workgroup holding a few columns over all rows.
+//     Beyond: panel_kernel (P workgroups, all resident at once): the (n - j) x jb
+//     panel is held in LDS for the whole panel, 128 consecutive rows per
 //     workgroup.  In each workgroup one wavefront runs the chain that decides the
 //     pivots (receive the candidates of column c, select, exchange rows, scale
 //     column c, update column c + 1, publish the candidate of column c + 1) with
@@ -20,9 +22,7 @@
 //  3. trailing update A22 -= L21 U12 with the MFMA GEMM.
 //  Steps 2 and 3 run first for the next panel's columns only; for all other
 //  columns they run on a second stream while the next panel is factored
-//  (lookahead of depth one).  Beside the Schur product (below), a panel of 64
-//  rows per workgroup and at least 10 workgroups does steps 2 and 3 for its own
-//  columns itself, before its chain starts (the fused form of panel_kernel).
+//  (lookahead of depth one).
 //
 // Cross-workgroup data is written with agent-scope stores and read with agent-scope
 // loads, which are coherent across the XCDs' separate L2 caches.  Every wait is
@@ -50,12 +50,10 @@
 #define SENT 0xFFFFFFFFFFFFFFFFULL  // empty exchange word (all ones)
 #define SNT 448                   // threads per panel workgroup: one chain + SNB bulk wavefronts
 #define SNB 6
-#define PANEL_RPL1_PMAX 32        // 64 rows per workgroup while P stays within this, else 128
-#define PANEL_LDS(rpl) ((size_t)LU_NB * (64 * (rpl) + 1) * sizeof(cplx))
 // LDS requested by every panel launch: more than 160 KB minus any GEMM workgroup's
 // share, so that no workgroup of the concurrent trailing update lands on a CU that
-// runs a panel workgroup (the chain wavefront would lose issue slots)
-#define PANEL_LDS_ALLOC PANEL_LDS(2)
+// runs a panel workgroup (the chain would lose issue slots)
+#define PANEL_LDS_ALLOC ((size_t)LU_NB * (128 + 1) * sizeof(cplx))
 
 // Slot buffer layout: per column c, the P records of rec = jb + 1 complex values
 // (candidate row, then its value and row index) followed by the diagonal row, and,
@@ -63,10 +61,7 @@
 // side (16 bytes each: one poll instruction of the chain reads P / 8 cache lines).
 #define SLOT_REC_ELEMS ((size_t)LU_NB * (PANEL_PMAX * (LU_NB + 1) + LU_NB))
 #define SLOT_HDR ((int)SLOT_REC_ELEMS)  // header of column c, workgroup g: SLOT_HDR + c P + g
-// after the headers, the U12 block (LU_NB x LU_NB, column-major) of a panel that
-// applies the previous panel's update to its own columns (the fused form below)
-#define SLOT_U12 ((int)(SLOT_REC_ELEMS + (size_t)LU_NB * PANEL_PMAX))
-#define SLOT_ELEMS ((size_t)SLOT_U12 + (size_t)LU_NB * LU_NB)  // complex values per slot buffer
+#define SLOT_ELEMS (SLOT_REC_ELEMS + (size_t)LU_NB * PANEL_PMAX)  // complex values per slot buffer
 
 // 16-byte agent-coherent loads and stores of the exchange records: buffer
 // instructions with the sc1 cache-policy bit (agent scope on gfx94x / gfx950).
@@ -105,6 +100,15 @@ __device__ inline cplx rec_poll(__amdgpu_buffer_rsrc_t r, int elem, int32_t *dev
     v = rec_load(r, elem);
   }
   return rec_value(v);
+}
+
+// the words a panel of the next launch uses in its buffer back to the empty pattern:
+// the first n elements and the first h of the headers
+__device__ inline void slots_refill(cplx *slots, long n, int h, int i0, int step) {
+  st_v2 *ns = (st_v2 *)slots;
+  const double e = __longlong_as_double((long long)SENT);
+  for (long i = i0; i < n; i += step) ns[i] = st_v2{e, e};
+  for (int i = i0; i < h; i += step) ns[SLOT_HDR + i] = st_v2{e, e};
 }
 
 // Wave-wide maximum of a double by DPP row operations (a few ALU cycles per step,
@@ -157,17 +161,18 @@ __device__ inline cplx readlane_c(cplx v, int l) { return cmk(readlane_f64(v.x, 
 // component-wise select (keeps register arrays out of memory)
 __device__ inline cplx csel(bool c, cplx a, cplx b) { return cmk(c ? a.x : b.x, c ? a.y : b.y); }
 
-// 1/u for the pivot: the larger component is scaled to [0.5, 1) by an exact power
-// of two, then conj(u) / |u|^2 with a Newton-refined hardware reciprocal
+// 1/u for the pivot: u scaled by the power of two that brings its larger component
+// into [1, 2) (built from the exponent bits: integer operations, on the path from one
+// pivot to the next), then conj(u) / |u|^2 with a Newton-refined hardware reciprocal
 __device__ inline cplx pivot_recip(cplx u) {
-  int e = 0;
-  (void)frexp(fmax(fabs(u.x), fabs(u.y)), &e);
-  const cplx us = cmk(ldexp(u.x, -e), ldexp(u.y, -e));
+  const int ex = max(__double2hiint(u.x) & 0x7fffffff, __double2hiint(u.y) & 0x7fffffff) & 0x7ff00000;
+  const double sc = __hiloint2double(0x7fe00000 - min(ex, 0x7fd00000), 0);
+  const cplx us = cmk(u.x * sc, u.y * sc);
   const double d = fma(us.x, us.x, us.y * us.y);
   double r = __builtin_amdgcn_rcp(d);
   r = fma(r, fma(-d, r, 1.0), r);
   r = fma(r, fma(-d, r, 1.0), r);
-  r = ldexp(r, -e);
+  r *= sc;
   return cmk(us.x * r, -us.y * r);
 }
 
@@ -192,33 +197,13 @@ __device__ inline cplx pivot_recip(cplx u) {
 //   slots[c * cstride + g * rs]  record of workgroup g: (value, row), then the row
 //   slots[c * cstride + P * rs]  the diagonal row j + c, by its owner
 //   slots[SLOT_HDR + c * P + g]  the header (value, row) of workgroup g when packed
-typedef double pdbl4 __attribute__((ext_vector_type(4)));
-__device__ inline pdbl4 pmfma16(double a, double b, pdbl4 c) {
-  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-}
-
-// FUSE: the panel first applies the previous panel's update to its own columns
-// (what the separate interchange/TRSM and k = 64 update launches do otherwise):
-// the previous panel (columns j0 .. j0 + 63, interchange list swp0) gives
-//   U12 = L11^{-1} (its interchanged rows j0 .. j0 + 63 of these columns),
-//   each row r >= j:  a_r = (row sigma(r) of these columns) - L(r, j0..) U12,
-// sigma the interchanges' row sources.  Every workgroup solves the columns
-// c = g (mod P) of U12 (lane = row, one column per wavefront) and publishes them
-// in the slot buffer's U12 block with the exchange protocol (agent-scope stores
-// over the empty pattern, polled by the readers); every workgroup then reads all
-// of U12 and forms its rows' update on the FP64 matrix cores.  Rows j0 .. j0 + 63
-// of these columns (U12 itself) are written back by workgroup 0 at the end, when
-// every workgroup has long finished reading the old values (it has published its
-// candidate of column 0, which workgroup 0 waited for).  RPL = 1 and P >= 10 only.
 // (BAT: a batch of problems, blockIdx.y selecting the problem's matrix, pivots,
 // flags, exchange slots and interchange list from bb)
-template <int RPL, bool FUSE, class T, bool BAT = false>
+template <class T, bool BAT>
 __global__ __launch_bounds__(SNT) void panel_kernel(int N, T *A, long lda, int j, int jb, int P, int32_t *ipiv,
-                                                    int32_t *dev_err, cplx *slots, cplx *next_slots, int next_P,
-                                                    int next_jb, int32_t *swp, int j0, const int32_t *swp0,
-                                                    bm_lu_batch bb) {
+                                                    int32_t *dev_err, cplx *slots, cplx *next_slots, long fill_n,
+                                                    int fill_h, int32_t *swp, bm_lu_batch bb) {
   if constexpr (BAT) {
-    static_assert(!FUSE, "batched panels: no fused update");
     const int b = blockIdx.y;
     A = (T *)bb.A[b];
     ipiv = bb.ipiv[b];
@@ -227,7 +212,7 @@ __global__ __launch_bounds__(SNT) void panel_kernel(int N, T *A, long lda, int j
     next_slots = bb.nxt[b];
     swp = bb.swp[b];
   }
-  constexpr int RPW = 64 * RPL;  // rows per workgroup
+  constexpr int RPL = 2, RPW = 64 * RPL;  // rows per workgroup
   constexpr int LDP = RPW + 1;   // column stride of the LDS panel (odd: conflict-free row reads)
   extern __shared__ cplx pan[];  // jb x LDP
   __shared__ cplx urow[2][LU_NB];  // pivot row of column c, for the bulk wavefronts
@@ -246,153 +231,7 @@ __global__ __launch_bounds__(SNT) void panel_kernel(int N, T *A, long lda, int j
   const int nv = (N - r0 >= RPW) ? RPW : ((N - r0 > 0) ? (int)(N - r0) : 0);
   bool ok = true;
 
-  if constexpr (FUSE) {
-    static_assert(RPL == 1, "the fused update holds U12 beside a 64-row panel");
-    static_assert(sizeof(T) == sizeof(cplx), "the fused update is built for the FP64 factorisation");
-    constexpr int UOFF = LU_NB * (64 + 1);  // U12 in LDS after the panel block
-    cplx *Ls = pan;                         // L11, then this workgroup's rows of L21 (ld 64)
-    cplx *Us = pan + UOFF;                  // all of U12 (ld 64)
-    __shared__ int s_src[64], s_srcx[64];   // row sources of rows r0 + i and j0 + i
-    if (tid < 64) {
-      s_src[tid] = (int)r0 + tid;
-      s_srcx[tid] = j0 + tid;
-    }
-    __syncthreads();
-    {
-      const int np = swp0[0];
-      for (int e = tid; e < np; e += SNT) {
-        const int dst = swp0[1 + 2 * e], src = swp0[2 + 2 * e];
-        if (dst >= r0 && dst < r0 + 64) s_src[dst - r0] = src;
-        if (dst >= j0 && dst < j0 + 64) s_srcx[dst - j0] = src;
-      }
-    }
-    // L11 of the previous panel into LDS; each wavefront's column of U12 (its
-    // interchanged rows j0 .. j0 + 63) into registers
-    for (int idx = tid; idx < LU_NB * LU_NB; idx += SNT) {
-      const int r = idx & 63, c = idx >> 6;
-      st_st(Ls, idx, ld_z(A, (long)(j0 + r) + (long)(j0 + c) * lda));
-    }
-    __syncthreads();
-    const int cown = g + P * wave;  // this wavefront's column of U12
-    if (wave < SNT / 64 && cown < jb) {
-      const st_v2 x0 = ld_z(A, (long)s_srcx[lane] + (long)(j + cown) * lda);
-      cplx x = cmk(x0.x, x0.y);
-      for (int c0 = 0; c0 < LU_NB - 1; c0 += 8) {
-        cplx lv[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          const int c = c0 + u;
-          lv[u] = (c < LU_NB - 1 && lane > c) ? Ls[c * 64 + lane] : cmk(0.0, 0.0);
-        }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          const int c = c0 + u;
-          if (c < LU_NB - 1) x = cfms(x, lv[u], readlane_c(x, c));
-        }
-      }
-      rec_store(rs, SLOT_U12 + cown * 64 + lane, x);
-    }
-    // (columns c = g + P w, w < 7 wavefronts: all of jb <= 64 are covered when P >= 10)
-    __syncthreads();  // every wavefront done with L11
-    // all of U12 (every load in flight, then polled until written), and this
-    // workgroup's rows of L21, into LDS
-    {
-      constexpr int UPT = (LU_NB * LU_NB + SNT - 1) / SNT;
-      bm_v4i uv[UPT];
-#pragma unroll
-      for (int q = 0; q < UPT; ++q) {
-        const int idx = tid + SNT * q;
-        if (idx < LU_NB * jb) uv[q] = rec_load(rs, SLOT_U12 + idx);
-      }
-#pragma unroll
-      for (int q = 0; q < UPT; ++q) {
-        const int idx = tid + SNT * q;
-        if (idx < LU_NB * LU_NB) {
-          const int r = idx & 63, kc = idx >> 6;  // L21: row r, column kc of the previous panel
-          st_st(Ls, kc * 64 + r, (r < nv) ? ld_z(A, (r0 + r) + (long)(j0 + kc) * lda) : st_v2{0.0, 0.0});
-        }
-      }
-      const unsigned long long t0 = wall_clock64();
-      for (;;) {
-        bool all = true;
-#pragma unroll
-        for (int q = 0; q < UPT; ++q) {
-          const int idx = tid + SNT * q;
-          if (idx < LU_NB * jb && rec_empty(uv[q])) {
-            all = false;
-            uv[q] = rec_load(rs, SLOT_U12 + idx);
-          }
-        }
-        if (all) break;
-        if (!ok || wait_expired(t0)) {
-          if (ok) atomicOr(dev_err, 1);
-          ok = false;
-          break;
-        }
-        __builtin_amdgcn_s_sleep(1);
-      }
-#pragma unroll
-      for (int q = 0; q < UPT; ++q) {
-        const int idx = tid + SNT * q;
-        if (idx < LU_NB * LU_NB) Us[idx] = (idx < LU_NB * jb) ? rec_value(uv[q]) : cmk(0.0, 0.0);
-      }
-    }
-    __syncthreads();
-    // this workgroup's rows: (row sigma(r) of these columns) - L21 U12; wavefronts
-    // 0 .. 3 each own a 32 x 32 quarter (2 x 2 blocks of 16 x 16 MFMA results:
-    // lane l, register q -> row l % 16, column 4 q + l / 16 of a block)
-    pdbl4 accr[2][2], acci[2][2];
-    const int wm = wave & 1, wn = (wave >> 1) & 1, fq = lane >> 4, fi = lane & 15;
-    if (wave < 4) {
-#pragma unroll
-      for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-          accr[a][b] = (pdbl4){0, 0, 0, 0};
-          acci[a][b] = (pdbl4){0, 0, 0, 0};
-        }
-      for (int k4 = 0; k4 < LU_NB; k4 += 4) {
-        cplx av[2], bv[2];
-#pragma unroll
-        for (int a = 0; a < 2; ++a) av[a] = Ls[(k4 + fq) * 64 + wm * 32 + a * 16 + fi];
-#pragma unroll
-        for (int b = 0; b < 2; ++b) bv[b] = Us[(wn * 32 + b * 16 + fi) * 64 + k4 + fq];
-#pragma unroll
-        for (int a = 0; a < 2; ++a)
-#pragma unroll
-          for (int b = 0; b < 2; ++b) {
-            accr[a][b] = pmfma16(bv[b].x, av[a].x, accr[a][b]);
-            acci[a][b] = pmfma16(bv[b].y, av[a].x, acci[a][b]);
-            accr[a][b] = pmfma16(bv[b].y, -av[a].y, accr[a][b]);
-            acci[a][b] = pmfma16(bv[b].x, av[a].y, acci[a][b]);
-          }
-      }
-    }
-    __syncthreads();  // L21 read by every wavefront before the panel block overwrites it
-    if (wave < 4) {
-      st_v2 old[2][2][4];
-#pragma unroll
-      for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const int r = wm * 32 + a * 16 + fi, c = wn * 32 + b * 16 + 4 * q + fq;
-            old[a][b][q] = ld_z(A, (r < nv && c < jb) ? (long)s_src[r] + (long)(j + c) * lda : (long)j + (long)j * lda);
-          }
-#pragma unroll
-      for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const int r = wm * 32 + a * 16 + fi, c = wn * 32 + b * 16 + 4 * q + fq;
-            if (c < jb)
-              st_st(pan, c * LDP + r,
-                    (r < nv) ? st_v2{old[a][b][q].x - accr[a][b][q], old[a][b][q].y - acci[a][b][q]} : st_v2{0.0, 0.0});
-          }
-    }
-  } else {
+  {
     // the workgroup's block of the panel into LDS: each thread's loads in one
     // batch (unconditional, an item outside the block reads the panel's first
     // element), then the LDS stores
@@ -753,33 +592,10 @@ __global__ __launch_bounds__(SNT) void panel_kernel(int N, T *A, long lda, int j
     const int r = idx % RPW, c = idx / RPW;
     if (r < nv) st_z(A, (r0 + r) + (long)(j + c) * lda, to_v2(pan[c * LDP + r]));
   }
-  // refill the words the next panel uses in the other slot buffer with the empty pattern
-  if (next_P > 0) {
-    const int nrec = next_jb + 1, nrstr = nrec;
-    const int ncstr = next_P * nrec + next_jb;
-    const int per_col = next_P * nrec + next_jb;
-    unsigned long long *ns = (unsigned long long *)next_slots;
-    for (int idx = g * SNT + tid; idx < next_jb * per_col; idx += P * SNT) {
-      const int col = idx / per_col, rem = idx % per_col;
-      const int el = col * ncstr + ((rem < next_P * nrec) ? (rem / nrec) * nrstr + rem % nrec
-                                                           : next_P * nrstr + (rem - next_P * nrec));
-      ns[2 * (size_t)el] = SENT;
-      ns[2 * (size_t)el + 1] = SENT;
-    }
-    for (int idx = g * SNT + tid; idx < 2 * next_jb * next_P; idx += P * SNT) ns[2 * (size_t)SLOT_HDR + idx] = SENT;
-    for (int idx = g * SNT + tid; idx < 2 * LU_NB * LU_NB; idx += P * SNT) ns[2 * (size_t)SLOT_U12 + idx] = SENT;
-  }
-  if constexpr (FUSE) {
-    // U12: rows j0 .. j0 + 63 of this panel's columns
-    if (g == 0) {
-      const cplx *Us = pan + LU_NB * (64 + 1);
-      for (int idx = tid; idx < LU_NB * jb; idx += SNT) {
-        const int k = idx & 63, cc = idx >> 6;
-        st_z(A, (long)(j0 + k) + (long)(j + cc) * lda, to_v2(Us[cc * 64 + k]));
-      }
-    }
-  }
+  slots_refill(next_slots, fill_n, fill_h, g * SNT + tid, P * SNT);
 }
+
+#include "bm_panel_stream.h"
 
 // ---------------------------------------------------------------------------
 // 2. row interchanges outside the panel, and U12 = L11^{-1} A12
@@ -976,20 +792,19 @@ __global__ void diag_inv_kernel(int n, const TS *LU, long ld, cplx *dinv);
 #define TI_LDS ((size_t)(2 * TI_N * (TI_N + 1) + 1024) * sizeof(cplx))  // M, X, T of tri_inv64
 
 template <class T>
-using panel_fn = void (*)(int, T *, long, int, int, int, int32_t *, int32_t *, cplx *, cplx *, int, int, int32_t *,
-                          int, const int32_t *, bm_lu_batch);
-// 64 and 128 rows per workgroup; 64 rows with the previous panel's update fused
-// (FP64 storage only)
-static const panel_fn<cplx> panel_fns[3] = {panel_kernel<1, false, cplx>, panel_kernel<2, false, cplx>,
-                                            panel_kernel<1, true, cplx>};
-static const panel_fn<cplx32> panel_fns_c64[2] = {panel_kernel<1, false, cplx32>, panel_kernel<2, false, cplx32>};
-static const panel_fn<cplx> panel_fns_bat[2] = {panel_kernel<1, false, cplx, true>, panel_kernel<2, false, cplx, true>};
-static const panel_fn<cplx32> panel_fns_bat_c64[2] = {panel_kernel<1, false, cplx32, true>,
-                                                      panel_kernel<2, false, cplx32, true>};
-static const void *panel_bat_of(const cplx *, int k) { return (const void *)panel_fns_bat[k]; }
-static const void *panel_bat_of(const cplx32 *, int k) { return (const void *)panel_fns_bat_c64[k]; }
-static const void *panel_fn_of(const cplx *, int k) { return (const void *)panel_fns[k]; }
-static const void *panel_fn_of(const cplx32 *, int k) { return (k < 2) ? (const void *)panel_fns_c64[k] : nullptr; }
+using panel_fn = void (*)(int, T *, long, int, int, int, int32_t *, int32_t *, cplx *, cplx *, long, int, int32_t *,
+                          bm_lu_batch);
+// By kind of panel (lu_shape): the streaming panels by rows per thread and columns
+// per workgroup, then the exchanging panel.
+#define PANEL_KINDS 5
+template <class T, bool BAT>
+static panel_fn<T> panel_fn_of(int kind) {
+  static const panel_fn<T> fns[PANEL_KINDS] = {
+      panel_stream_kernel<64, 1, 8, T, BAT>,  panel_stream_kernel<256, 2, 4, T, BAT>,
+      panel_stream_kernel<512, 2, 4, T, BAT>, panel_stream_kernel<512, 4, 4, T, BAT>,
+      panel_kernel<T, BAT>};
+  return fns[kind];
+}
 
 static int panel_attr_done[64];
 
@@ -1009,16 +824,48 @@ int bm_fill_u64(hipStream_t s, void *p, size_t n, unsigned long long v) {
   return BM_OK;
 }
 
-// rows per lane of the chain wavefront (1: 64, 2: 128 rows per workgroup) and the
-// workgroup count of a panel of R rows: 64 rows per workgroup while that keeps
-// P <= PANEL_RPL1_PMAX, else 128
-static bool panel_shape(int R, int ncu, int *rpl, int *P_out) {
+// How the panel of R rows and jb columns runs: kind of kernel (panel_fn_of), its
+// workgroups, and the exchange words it uses (slots_refill).  The streaming panel
+// holds (rows per thread) x (columns per workgroup) values in a thread's registers.
+// Per 64-column panel (us, alone on the device; threads x rows per thread x columns
+// per workgroup):
+//   rows      streaming                            exchanging (64 or 128 rows/workgroup)
+//     64       47 (64x1x8)                          135
+//    512       60 (256x2x4), 65 (512x1x4)           130
+//   1024       72 (512x2x4), 77 (x8), 76 (256x4x4)  130
+//   2048       94 (512x4x4), 108 (x2), 125 (1024x2x4)  131 to 155
+//   4096      167 (512x8x4), 386 (512x8x2, spilled) 152
+// so beyond 2048 rows, where a thread's rows no longer leave registers for the
+// clerk's wavefront, the exchanging panel (128 rows per workgroup) takes over.
+struct lu_shape {
+  int kind, wgs, threads, fill_h;
+  long fill_n;
+  size_t lds;
+};
+#define PANEL_STREAM_MAX_R 2048
+static bool panel_shape(int R, int jb, int ncu, lu_shape *o) {
+  // (the exchanging panel's workgroup count bounds the orders taken, whichever runs)
   const int pmax = (ncu < PANEL_PMAX) ? ncu : PANEL_PMAX;
-  int k = (R <= 64 * PANEL_RPL1_PMAX) ? 1 : 2;
-  const int P = (R + 64 * k - 1) / (64 * k);
-  if (P < 1 || P > pmax) return false;
-  *rpl = k;
-  *P_out = P;
+  const int P = (R + 127) / 128;
+  if (P < 1 || ((R > 2048) ? P : (R + 63) / 64) > pmax) return false;
+  if (R <= PANEL_STREAM_MAX_R) {
+    static const int cw[PANEL_KINDS - 1] = {8, 4, 4, 4}, nt[PANEL_KINDS - 1] = {64, 256, 512, 512};
+    int k = (R <= LU_NB) ? 0 : 1;
+    while (k > 0 && R > (256 << k)) ++k;
+    o->kind = k;
+    o->wgs = (jb + cw[k] - 1) / cw[k];
+    o->threads = nt[k] + 64;
+    o->lds = SPN_LDS_ALLOC;
+    o->fill_n = (long)jb * R;
+    o->fill_h = jb;
+  } else {
+    o->kind = PANEL_KINDS - 1;
+    o->wgs = P;
+    o->threads = SNT;
+    o->lds = PANEL_LDS_ALLOC;
+    o->fill_n = (long)jb * ((long)P * (jb + 1) + jb);
+    o->fill_h = jb * P;
+  }
   return true;
 }
 
@@ -1034,13 +881,16 @@ int bm_getrf_prepare() {
   int dev = 0;
   BM_HIP_TRY(hipGetDevice(&dev));
   if (dev >= 0 && dev < 64 && !panel_attr_done[dev]) {
-    const void *big[] = {(const void *)panel_fns[0],     (const void *)panel_fns[1],
-                         (const void *)panel_fns[2],     (const void *)panel_fns_c64[0],
-                         (const void *)panel_fns_c64[1], (const void *)panel_fns_bat[0],
-                         (const void *)panel_fns_bat[1], (const void *)panel_fns_bat_c64[0],
-                         (const void *)panel_fns_bat_c64[1]};
-    for (const void *f : big)
-      BM_HIP_TRY(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)PANEL_LDS_ALLOC));
+    const void *big[4 * PANEL_KINDS];
+    for (int k = 0; k < PANEL_KINDS; ++k) {
+      big[4 * k] = (const void *)panel_fn_of<cplx, false>(k);
+      big[4 * k + 1] = (const void *)panel_fn_of<cplx, true>(k);
+      big[4 * k + 2] = (const void *)panel_fn_of<cplx32, false>(k);
+      big[4 * k + 3] = (const void *)panel_fn_of<cplx32, true>(k);
+    }
+    for (int i = 0; i < 4 * PANEL_KINDS; ++i)
+      BM_HIP_TRY(hipFuncSetAttribute(big[i], hipFuncAttributeMaxDynamicSharedMemorySize,
+                                     (int)(i < 4 * (PANEL_KINDS - 1) ? SPN_LDS_ALLOC : PANEL_LDS_ALLOC)));
     const void *st_next[] = {(const void *)swap_trsm_kernel<ST_CW_NEXT, cplx>,
                              (const void *)swap_trsm_kernel<ST_CW_NEXT, cplx32>,
                              (const void *)swap_trsm_kernel<ST_CW_NEXT, cplx, true>,
@@ -1103,9 +953,9 @@ static int lu_update(hipStream_t st, T *A, long lda, int n, int j, int jb, const
   return BM_OK;
 }
 
-// Common start of a factorisation: panel shapes (rows per lane, workgroups) and
+// Common start of a factorisation: panel shapes and
 // the device flags and the first panel's exchange words reset.
-static int lu_begin(hipStream_t s, int n, int32_t *dev_err, bm_getrf_ws *w, int *shape, int *ncu_out) {
+static int lu_begin(hipStream_t s, int n, int32_t *dev_err, bm_getrf_ws *w, lu_shape *shape, int *ncu_out) {
   if (int rc0 = bm_getrf_prepare()) return rc0;
   int dev = 0;
   BM_HIP_TRY(hipGetDevice(&dev));
@@ -1117,13 +967,11 @@ static int lu_begin(hipStream_t s, int n, int32_t *dev_err, bm_getrf_ws *w, int 
   if (npanel > 1024) return BM_E_ARG;
   for (int pi = 0; pi < npanel; ++pi) {
     const int R = n - pi * LU_NB;
-    if (!panel_shape(R, ncu, &shape[3 * pi], &shape[3 * pi + 1])) return BM_E_ARG;
+    if (!panel_shape(R, (R < LU_NB) ? R : LU_NB, ncu, &shape[pi])) return BM_E_ARG;
   }
   if (npanel > 0) {  // the first panel's words of slot buffer 0; each panel refills the next one's
-    const int jb0 = (n < LU_NB) ? n : LU_NB;
-    const size_t cstr0 = (size_t)shape[1] * (jb0 + 1) + jb0;
-    if (int rc0 = bm_fill_u64(s, w->slots, 2 * (size_t)jb0 * cstr0, ~0ull)) return rc0;
-    if (int rc0 = bm_fill_u64(s, w->slots + SLOT_HDR, 2 * (size_t)jb0 * shape[1], ~0ull)) return rc0;
+    if (int rc0 = bm_fill_u64(s, w->slots, 2 * (size_t)shape[0].fill_n, ~0ull)) return rc0;
+    if (int rc0 = bm_fill_u64(s, w->slots + SLOT_HDR, 2 * (size_t)shape[0].fill_h, ~0ull)) return rc0;
   }
   return BM_OK;
 }
@@ -1134,40 +982,19 @@ static int lu_begin(hipStream_t s, int n, int32_t *dev_err, bm_getrf_ws *w, int 
 // launch avoids the start and drain cost of a cooperative launch.  Every wait in
 // the kernel is bounded, so a launch whose workgroups cannot all become resident
 // ends with BM_E_DEVICE, not a hang.)
-// whether panel pi applies the previous panel's update to its own columns itself
-// (64 rows per workgroup, enough workgroups to solve U12 one column per wavefront).
-// Only in the factorisation beside the Schur product, where the two separate
-// launches it replaces wait for CUs held by the product's other work; alone on
-// the device they are as fast (measured: the plain 4096 x 4096 LU 11.05 ms with
-// them, 11.15 ms fused; star2048 beside the product 6.86 ms per step with them,
-// 6.79 ms fused).
-static bool lu_fused(bool overlap, const int *shape, int pi) {
-  return overlap && pi >= 1 && shape[3 * pi] == 1 && shape[3 * pi + 1] >= 10;
-}
-
 template <class T>
 static int lu_panel(hipStream_t s, int n, T *A, int64_t lda, int32_t *ipiv, int32_t *dev_err, bm_getrf_ws *w,
-                    const int *shape, int pi, bool overlap) {
+                    const lu_shape *shape, int pi) {
   const int npanel = (n + LU_NB - 1) / LU_NB;
   const int j = pi * LU_NB, jb = (n - j < LU_NB) ? n - j : LU_NB;
-  int P = shape[3 * pi + 1];
-  int next_P = 0, next_jb = 0;
-  if (pi + 1 < npanel) {
-    next_jb = (n - j - LU_NB < LU_NB) ? n - j - LU_NB : LU_NB;
-    next_P = shape[3 * (pi + 1) + 1];
-  }
-  cplx *cur = w->slots + (size_t)(pi & 1) * SLOT_ELEMS, *nxt = w->slots + (size_t)((pi + 1) & 1) * SLOT_ELEMS;
-  int32_t *swp = w->swp + (size_t)pi * SWP_STRIDE;
-  long ldal = (long)lda;
-  int nn = n, jj = j, jbb = jb;
-  const bool fuse = lu_fused(overlap, shape, pi);
-  int j0 = fuse ? j - LU_NB : 0;
-  const int32_t *swp0 = fuse ? w->swp + (size_t)(pi - 1) * SWP_STRIDE : swp;
-  bm_lu_batch bb{};
-  void *args[] = {&nn, &A, &ldal, &jj, &jbb, &P, &ipiv, &dev_err, &cur, &nxt, &next_P, &next_jb, &swp, &j0, &swp0, &bb};
-  const int rpl = shape[3 * pi];
+  const bool more = pi + 1 < npanel;
   if (w->prof) bm_phase_begin(w->prof, BM_PH_PANEL);
-  BM_HIP_TRY(hipLaunchKernel(panel_fn_of(A, fuse ? 2 : rpl - 1), dim3(P), dim3(SNT), args, PANEL_LDS_ALLOC, s));
+  hipLaunchKernelGGL((panel_fn_of<T, false>(shape[pi].kind)), dim3(shape[pi].wgs), dim3(shape[pi].threads),
+                     shape[pi].lds, s, n, A, (long)lda, j, jb, shape[pi].wgs, ipiv, dev_err,
+                     w->slots + (size_t)(pi & 1) * SLOT_ELEMS, w->slots + (size_t)((pi + 1) & 1) * SLOT_ELEMS,
+                     more ? shape[pi + 1].fill_n : 0L, more ? shape[pi + 1].fill_h : 0,
+                     w->swp + (size_t)pi * SWP_STRIDE, bm_lu_batch{});
+  BM_HIP_TRY(hipGetLastError());
   if (w->prof) bm_phase_end(w->prof, BM_PH_PANEL);
   return BM_OK;
 }
@@ -1176,7 +1003,7 @@ template <class T>
 static int getrf_run(hipStream_t s, int n, T *A, int64_t lda, int32_t *ipiv, int32_t *dev_err, bm_getrf_ws *w,
                      int gemm32) {
   if (!w || w->n < n) return BM_E_ARG;
-  int shape[3 * 1024];  // rows per lane, P per panel
+  lu_shape shape[1024];
   int ncu = 0;
   if (int rc0 = lu_begin(s, n, dev_err, w, shape, &ncu)) return rc0;
   const int npanel = (n + LU_NB - 1) / LU_NB;
@@ -1184,7 +1011,7 @@ static int getrf_run(hipStream_t s, int n, T *A, int64_t lda, int32_t *ipiv, int
   const bool la = w->aux != nullptr;
   for (int j = 0, pi = 0; j < n; j += LU_NB, ++pi) {
     const int jb = (n - j < LU_NB) ? n - j : LU_NB;
-    if (int rc = lu_panel(s, n, A, lda, ipiv, dev_err, w, shape, pi, false)) return rc;
+    if (int rc = lu_panel(s, n, A, lda, ipiv, dev_err, w, shape, pi)) return rc;
     const int32_t *swp = w->swp + (size_t)pi * SWP_STRIDE;
     // Lookahead: the stream s applies the panel's interchanges and its update to the
     // next panel's columns only; the auxiliary stream applies them to every other
@@ -1262,12 +1089,12 @@ static int getrf_run_batch(hipStream_t s, int n, int count, T *const *A, int64_t
   if (count < 1 || count > BM_LU_BATCH_MAX || n < 1 || lda < n) return BM_E_ARG;
   for (int b = 0; b < count; ++b)
     if (!ws[b] || ws[b]->n < n || !A[b] || !ipiv[b] || !dev_err[b]) return BM_E_ARG;
-  int shape[3 * 1024];
+  lu_shape shape[1024];
   int ncu = 0;
   for (int b = 0; b < count; ++b)  // per problem: flags and the first panel's exchange words
     if (int rc0 = lu_begin(s, n, dev_err[b], ws[b], shape, &ncu)) return rc0;
   // every workgroup of a batched panel must be resident at once
-  if ((long)count * shape[1] > ncu) return BM_E_ARG;
+  if ((long)count * ((n > 2048) ? (n + 127) / 128 : (n + 63) / 64) > ncu) return BM_E_ARG;
   bm_getrf_ws *w = ws[0];
   const bool la = w->aux != nullptr;
   bm_lu_batch bb{};
@@ -1280,27 +1107,17 @@ static int getrf_run_batch(hipStream_t s, int n, int count, T *const *A, int64_t
   const int npanel = (n + LU_NB - 1) / LU_NB;
   for (int j = 0, pi = 0; j < n; j += LU_NB, ++pi) {
     const int jb = (n - j < LU_NB) ? n - j : LU_NB;
-    int P = shape[3 * pi + 1], next_P = 0, next_jb = 0;
-    if (pi + 1 < npanel) {
-      next_jb = (n - j - LU_NB < LU_NB) ? n - j - LU_NB : LU_NB;
-      next_P = shape[3 * (pi + 1) + 1];
-    }
     for (int b = 0; b < count; ++b) {
       bb.cur[b] = ws[b]->slots + (size_t)(pi & 1) * SLOT_ELEMS;
       bb.nxt[b] = ws[b]->slots + (size_t)((pi + 1) & 1) * SLOT_ELEMS;
       bb.swp[b] = ws[b]->swp + (size_t)pi * SWP_STRIDE;
     }
-    {
-      int nn = n, jj = j, jbb = jb, j0 = 0;
-      T *a0 = nullptr;
-      cplx *c0p = nullptr, *c1p = nullptr;
-      int32_t *p0 = nullptr, *e0 = nullptr, *s0 = nullptr;
-      const int32_t *sw0 = nullptr;
-      void *args[] = {&nn, &a0, (void *)&ldal, &jj, &jbb, &P, &p0, &e0, &c0p, &c1p, &next_P, &next_jb, &s0, &j0,
-                      &sw0, &bb};
-      BM_HIP_TRY(hipLaunchKernel(panel_bat_of((const T *)nullptr, shape[3 * pi] - 1), dim3(P, count), dim3(SNT), args,
-                                 PANEL_LDS_ALLOC, s));
-    }
+    const bool more = pi + 1 < npanel;
+    hipLaunchKernelGGL((panel_fn_of<T, true>(shape[pi].kind)), dim3(shape[pi].wgs, count), dim3(shape[pi].threads),
+                       shape[pi].lds, s, n, (T *)nullptr, ldal, j, jb, shape[pi].wgs, (int32_t *)nullptr,
+                       (int32_t *)nullptr, (cplx *)nullptr, (cplx *)nullptr, more ? shape[pi + 1].fill_n : 0L,
+                       more ? shape[pi + 1].fill_h : 0, (int32_t *)nullptr, bb);
+    BM_HIP_TRY(hipGetLastError());
     const int nr = n - j - jb;
     const int jn = j + jb, jbn = (nr < LU_NB) ? nr : LU_NB;
     if (la && pi > 0) BM_HIP_TRY(hipStreamWaitEvent(s, w->e_rest, 0));
@@ -1346,7 +1163,7 @@ int bm_getrf_run_batch_c64(hipStream_t s, int n, int count, cplx32 *const *A, in
 //
 // The segment widths come from a timing model of the device (one 64 x 64 tile of
 // depth k on a CU that holds one workgroup: 0.12 us per unit of k; a panel of the
-// chain: 0.15 ms; a catch-up step: 12 us plus its GEMM at 25 TFLOP/s): each
+// chain: see sp_plan; a catch-up step: 12 us plus its GEMM at 25 TFLOP/s): each
 // segment is the widest whose product and catch-up end before the panels reach
 // it, so that the chain never waits; a wrong model costs time, never correctness.
 // ---------------------------------------------------------------------------
@@ -1433,13 +1250,13 @@ static double sp_time(int tiles, int ks, int slots, int k, double per_k) {
   return rounds * per_k * kc + (ks > 1 ? 0.006 : 0.0);
 }
 
-// Returns 1 when the planned product ends before the chain of panels (the overlap
+// Returns 1 when, with a panel of the chain taking beta ms, the planned product ends before the chain of panels (the overlap
 // pays), else 0 (then the product is better formed in full first).
-static int sp_plan(int n, int k, int ncu, int gs, size_t w_cap, sp_seg *seg, int *nseg_out) {
+static int sp_plan_at(double beta, int n, int k, int ncu, int gs, size_t w_cap, sp_seg *seg, int *nseg_out) {
   const int B = (n + LU_NB - 1) / LU_NB, tb = B;  // blocks; row tiles of a block
   const double per_k1 = 0.49 / 4096.0;            // ms per unit of k: one workgroup per CU
   const double per_k2 = 0.84 / 4096.0;            // two per CU (block 0, whole device)
-  const double beta = 0.15 + 0.05 * ((n > 2048) ? (n - 2048) / 2048.0 : 0.0), margin = 0.03;
+  const double margin = 0.03;
   int nseg = 0;
   const int ks0 = sp_ksplit(tb, 2 * ncu, k, w_cap);
   const double t0 = sp_time(tb, ks0, 2 * ncu, k, per_k2);
@@ -1477,6 +1294,18 @@ static int sp_plan(int n, int k, int ncu, int gs, size_t w_cap, sp_seg *seg, int
   return (E <= t0 + beta * B - margin) ? 1 : 0;
 }
 
+// The plan for the shortest panel time that needs few segments.  A panel with the
+// launches to the next one takes 0.09 to 0.12 ms, but each segment's catch-up steps slow
+// the chain in ways the model leaves out, so a plan of many segments loses what it gains
+// (n = 1728: 9 segments 3.41 ms, 14 segments 4.30, 7 segments 3.74, product first 4.23;
+// n = 2048: 9 segments 4.72, 13 segments 5.45, 24 segments 7.35, product first 5.20).
+#define SP_FEW 10
+static int sp_plan(int n, int k, int ncu, int gs, size_t w_cap, sp_seg *seg, int *nseg_out) {
+  for (int i = 0; i <= 4; ++i)
+    if (sp_plan_at(0.09 + 0.015 * i, n, k, ncu, gs, w_cap, seg, nseg_out) && *nseg_out <= SP_FEW) return 1;
+  return 0;
+}
+
 int bm_getrf_schur_run(hipStream_t s, int n, cplx alpha, const cplx *bot, int64_t ldbot, const cplx *top,
                        int64_t ldtop, int k, cplx *A, int64_t lda, int32_t *ipiv, int32_t *dev_err, bm_getrf_ws *w,
                        cplx *W, size_t w_elems, int *nseg_out) {
@@ -1485,12 +1314,12 @@ int bm_getrf_schur_run(hipStream_t s, int n, cplx alpha, const cplx *bot, int64_
     return BM_E_ARG;
   *nseg_out = 0;
   bm_lu_pipe *q = w->pipe;
-  int shape[3 * SP_MAXB];
+  lu_shape shape[SP_MAXB];
   int ncu = 0;
   if (int rc0 = lu_begin(s, n, dev_err, w, shape, &ncu)) return rc0;
   const int B = (n + LU_NB - 1) / LU_NB;
   int pmax = 0;
-  for (int pi = 0; pi < B; ++pi) pmax = (shape[3 * pi + 1] > pmax) ? shape[3 * pi + 1] : pmax;
+  for (int pi = 0; pi < B; ++pi) pmax = (shape[pi].wgs > pmax) ? shape[pi].wgs : pmax;
   // the product's workgroups: one per CU, leaving free the largest panel's CUs and
   // SP_FREE_CUS more for the trailing updates and catch-ups (which share no CU
   // with the product)
@@ -1577,7 +1406,7 @@ int bm_getrf_schur_run(hipStream_t s, int n, cplx alpha, const cplx *bot, int64_
   if (int rc0 = issue(-1)) return rc0;
   for (int pi = 0; pi < B; ++pi) {
     const int j = pi * LU_NB, jb = (n - j < LU_NB) ? n - j : LU_NB;
-    if (int rc = lu_panel(s, n, A, lda, ipiv, dev_err, w, shape, pi, true)) return rc;
+    if (int rc = lu_panel(s, n, A, lda, ipiv, dev_err, w, shape, pi)) return rc;
     BM_HIP_TRY(hipEventRecord(q->ep[pi], s));
     if (int rc = issue(pi)) return rc;
     const int32_t *swp = w->swp + (size_t)pi * SWP_STRIDE;
@@ -1592,15 +1421,9 @@ int bm_getrf_schur_run(hipStream_t s, int n, cplx alpha, const cplx *bot, int64_
         hi = c1;
         if (i > 0 && seg[i].b0 == pi + 1) BM_HIP_TRY(hipStreamWaitEvent(s, q->ec[i], 0));  // joins now
       }
-    // (a fused next panel applies this update to its own columns; then nothing runs
-    // on s after the panel, and the other stream starts from the panel's own event)
-    if (!(pi + 1 < B && lu_fused(true, shape, pi + 1))) {
-      if (int rc = lu_update(s, A, ldal, n, j, jb, swp, 0, jn, jn + jbn, true, 0)) return rc;
-      BM_HIP_TRY(hipEventRecord(w->e_next, s));
-      BM_HIP_TRY(hipStreamWaitEvent(w->aux, w->e_next, 0));
-    } else {
-      BM_HIP_TRY(hipStreamWaitEvent(w->aux, q->ep[pi], 0));
-    }
+    if (int rc = lu_update(s, A, ldal, n, j, jb, swp, 0, jn, jn + jbn, true, 0)) return rc;
+    BM_HIP_TRY(hipEventRecord(w->e_next, s));
+    BM_HIP_TRY(hipStreamWaitEvent(w->aux, w->e_next, 0));
     for (int i = 1; i < nseg; ++i)
       if (seg[i].b0 == pi + 1) BM_HIP_TRY(hipStreamWaitEvent(w->aux, q->ec[i], 0));
     if (int rc = lu_update(w->aux, A, ldal, n, j, jb, swp, 0, jn + jbn, hi, false, 0)) return rc;
