@@ -109,6 +109,103 @@ __global__ __launch_bounds__(256) void gemv_partial_kernel(int m, int k, int nr,
   }
 }
 
+// Stage 1 for more than eight right-hand sides, on the FP64 matrix cores (the FP64
+// vector form above reads every element of B from LDS once per row and right-hand
+// side: 530 us for the 4096 x 8192 block with 32 of them, 1 TB/s of A).  A wavefront
+// owns 16 H rows and all right-hand sides, in groups of eight whose 16 real columns
+// [Re | Im] are the matrix instruction's columns (tile_mv8); lane (fi, fq) loads
+// A(row fi, k = fq) of each 4-deep step straight from memory, and the workgroup's
+// slice of B goes through LDS in operand order.  The steps of a slice of SK_KC are
+// loaded together, one slice ahead.  Solve with 32 right-hand sides, N = 4096: 1068 us
+// with H = 2 and slices of 16, 994 us with H = 1 and slices of 32 (more wavefronts per
+// SIMD; 1028 us with slices of 16 and 1024 workgroups).
+#define SK_ROWS 64  // rows per workgroup
+#define SK_KC 32
+#define SK_WG 512
+template <int NG, int H>
+__global__ __launch_bounds__(256) void skinny_partial_kernel(int m, int k, int nr, int kchunk, const cplx *A, long lda,
+                                                             const cplx *B, long ldb, cplx *part) {
+  constexpr int ST = SK_KC / 4;
+  __shared__ double Bs[2][ST * NG * 64];  // [step][group][lane]: the operand of the lane
+  const int tid = threadIdx.x, lane = tid & 63, fi = lane & 15, fq = lane >> 4;
+  const int r0 = (blockIdx.x * 4 + (tid >> 6)) * 16 * H;
+  const int ks = blockIdx.y;
+  const int k0 = ks * kchunk, k1 = (k0 + kchunk < k) ? k0 + kchunk : k;
+  tv_dbl4 c1[H][NG], c2[H][NG];
+#pragma unroll
+  for (int h = 0; h < H; ++h)
+#pragma unroll
+    for (int g = 0; g < NG; ++g) c1[h][g] = c2[h][g] = (tv_dbl4){0, 0, 0, 0};
+  // rows past m and columns past the slice read a valid address; the rows are not
+  // stored and the columns meet zero operands
+  long row[H];
+#pragma unroll
+  for (int h = 0; h < H; ++h) row[h] = (r0 + 16 * h + fi < m) ? r0 + 16 * h + fi : 0;
+  st_v2 av[H][ST];
+  auto load_a = [&](int kb) __attribute__((always_inline)) {
+#pragma unroll
+    for (int s = 0; s < ST; ++s) {
+      const int kk = kb + 4 * s + fq;
+#pragma unroll
+      for (int h = 0; h < H; ++h) av[h][s] = st_ld(A, row[h] + (long)(kk < k1 ? kk : k0) * lda);
+    }
+  };
+  // one value of B per thread and NG * ST * 64 / 256 of them
+  constexpr int BV = NG * ST / 4;
+  double bv[BV];
+  auto load_b = [&](int kb) __attribute__((always_inline)) {
+#pragma unroll
+    for (int q = 0; q < BV; ++q) {
+      const int e = tid + 256 * q, l = e & 63, g = (e >> 6) % NG, s = (e >> 6) / NG;
+      const int kk = kb + 4 * s + (l >> 4), r = 8 * g + (l & 7);
+      const double *p = (const double *)(B + ((kk < k1) ? kk : k0) + (long)((r < nr) ? r : 0) * ldb);
+      const double v = p[(l & 8) ? 1 : 0];
+      bv[q] = (kk < k1 && r < nr) ? v : 0.0;
+    }
+  };
+  load_b(k0);
+  load_a(k0);
+  int buf = 0;
+  for (int kb = k0; kb < k1; kb += SK_KC, buf ^= 1) {
+#pragma unroll
+    for (int q = 0; q < BV; ++q) Bs[buf][tid + 256 * q] = bv[q];
+    st_v2 at[H][ST];
+#pragma unroll
+    for (int h = 0; h < H; ++h)
+#pragma unroll
+      for (int s = 0; s < ST; ++s) at[h][s] = av[h][s];
+    if (kb + SK_KC < k1) {
+      load_b(kb + SK_KC);
+      load_a(kb + SK_KC);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < ST; ++s)
+#pragma unroll
+      for (int g = 0; g < NG; ++g) {
+        const double b = Bs[buf][(s * NG + g) * 64 + lane];
+#pragma unroll
+        for (int h = 0; h < H; ++h) {
+          c1[h][g] = __builtin_amdgcn_mfma_f64_16x16x4f64(b, at[h][s].x, c1[h][g], 0, 0, 0);
+          c2[h][g] = __builtin_amdgcn_mfma_f64_16x16x4f64(b, at[h][s].y, c2[h][g], 0, 0, 0);
+        }
+      }
+  }
+  cplx *pp = part + (size_t)ks * m * nr;
+#pragma unroll
+  for (int h = 0; h < H; ++h) {
+    const int i = r0 + 16 * h + fi;
+    if (i < m) {
+#pragma unroll
+      for (int g = 0; g < NG; ++g) {
+        const tv_dbl4 a = c1[h][g], b = c2[h][g];
+        if (8 * g + fq < nr) pp[i + (size_t)(8 * g + fq) * m] = cmk(a[0] - b[2], a[2] + b[0]);
+        if (8 * g + 4 + fq < nr) pp[i + (size_t)(8 * g + 4 + fq) * m] = cmk(a[1] - b[3], a[3] + b[1]);
+      }
+    }
+  }
+}
+
 __global__ void gemv_reduce_kernel(int m, int nr, int nsplit, const cplx *part, cplx *C, long ldc) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   const int r = blockIdx.y;
@@ -142,19 +239,28 @@ int bm_launch_gemv_sub(hipStream_t s, int m, int k, int nr, const cplx *A, int64
                        cplx *C, int64_t ldc, cplx *work) {
   if (m <= 0 || nr <= 0 || k <= 0) return BM_OK;
   if (nr > BM_MAX_NRHS) return BM_E_ARG;
-  const int rb = (m + GV_ROWS - 1) / GV_ROWS;
   int ns, kchunk;
   gemv_split(m, k, &ns, &kchunk);
-  const dim3 grid(rb, ns);
-  if (nr <= 8)
+  if (nr <= 8) {
+    const dim3 grid((m + GV_ROWS - 1) / GV_ROWS, ns);
     hipLaunchKernelGGL(gemv_partial_kernel<8>, grid, dim3(256), 0, s, m, k, nr, kchunk, A, (long)lda, B, (long)ldb,
                        work);
-  else if (nr <= 16)
-    hipLaunchKernelGGL(gemv_partial_kernel<16>, grid, dim3(256), 0, s, m, k, nr, kchunk, A, (long)lda, B, (long)ldb,
-                       work);
-  else
-    hipLaunchKernelGGL(gemv_partial_kernel<BM_MAX_NRHS>, grid, dim3(256), 0, s, m, k, nr, kchunk, A, (long)lda, B,
-                       (long)ldb, work);
+  } else {
+    // the matrix-core form: fewer, deeper slices (its partials are up to four times as
+    // wide), never more than the workspace holds
+    const int rb = (m + SK_ROWS - 1) / SK_ROWS;
+    int n2 = (SK_WG + rb - 1) / rb;
+    if (n2 > ns) n2 = ns;
+    kchunk = (((k + n2 - 1) / n2 + SK_KC - 1) / SK_KC) * SK_KC;
+    ns = (k + kchunk - 1) / kchunk;
+    const dim3 grid(rb, ns);
+    if (nr <= 16)
+      hipLaunchKernelGGL((skinny_partial_kernel<2, SK_ROWS / 64>), grid, dim3(256), 0, s, m, k, nr, kchunk, A, (long)lda, B, (long)ldb,
+                         work);
+    else
+      hipLaunchKernelGGL((skinny_partial_kernel<4, SK_ROWS / 64>), grid, dim3(256), 0, s, m, k, nr, kchunk, A, (long)lda, B, (long)ldb,
+                         work);
+  }
   BM_HIP_TRY(hipGetLastError());
   hipLaunchKernelGGL(gemv_reduce_kernel, dim3((m + 255) / 256, nr), dim3(256), 0, s, m, nr, ns, (const cplx *)work, C,
                      (long)ldc);
@@ -169,8 +275,11 @@ int bm_launch_gemv_sub(hipStream_t s, int m, int k, int nr, const cplx *A, int64
 // with WL_b = Linv_b L_{b,b-1} and WU_b = Uinv_b U_{b,b+1} formed beside the
 // inverses, so that only one block product lies between the arrival of the block
 // solved last before b and the publication of x_b.
-// One workgroup per block.  Blocks take tickets in launch order, so a workgroup
-// only waits for blocks held by workgroups that started before it.  The ticket
+// One workgroup per block and group of eight right-hand sides.  They take tickets in
+// launch order, block by block, so a workgroup only waits for workgroups that started
+// before it.  (The groups are independent chains of the same length; one workgroup
+// that took 32 right-hand sides ran four products between the arrival of a block and
+// its publication: 815 us per solve at N = 4096, with a workgroup per group 239 us.)  The ticket
 // counters and both solves' block areas share one buffer that a single fill with
 // the all-ones pattern prepares (a counter then starts at -1).  A solved block
 // is published to zbuf (pre-filled with an all-ones pattern) with agent-scope
@@ -183,26 +292,29 @@ int bm_launch_gemv_sub(hipStream_t s, int m, int k, int nr, const cplx *A, int64
 #define TS_NB BM_DIAG_NB
 #define ZSENT 0xFFFFFFFFFFFFFFFFULL
 
-// NG groups of eight right-hand sides (nrhs <= 8 NG): each lane holds 2 NG of them
-template <bool LOWER, int NG, class T>
+template <bool LOWER, class T>
 __global__ __launch_bounds__(256) void trsv_kernel(int n, const T *LU, long ld, const cplx *dinv, cplx *X, long ldx,
                                                    int nrhs, int32_t *ticket, cplx *zbuf, int32_t *dev_err) {
   __shared__ int s_t;
-  __shared__ cplx Z[TS_NB][8 * NG + 1];
-  const int nblk = (n + TS_NB - 1) / TS_NB;
+  __shared__ cplx Z[TS_NB][8 + 1];
+  const int nblk = (n + TS_NB - 1) / TS_NB, ngrp = (nrhs + 7) / 8;
   if (threadIdx.x == 0) s_t = atomicAdd(ticket, 1) + 1;  // the counter starts at -1
   __syncthreads();
-  const int t = s_t;
+  const int t = s_t / ngrp, g = s_t % ngrp;
   const int b = LOWER ? t : nblk - 1 - t;
   const int o = b * TS_NB;
   const int nb = (n - o < TS_NB) ? n - o : TS_NB;
+  // this group's right-hand sides
+  X += (long)(8 * g) * ldx;
+  zbuf += (size_t)g * 8 * TS_NB;
+  nrhs = (nrhs - 8 * g < 8) ? nrhs - 8 * g : 8;
   // lane (fi, fq) of wavefront w: row rr of the block; its right-hand sides are
-  // fq + 4 u (u = 2 g and 2 g + 1 for the group g of eight), as tile_mv8 leaves them
+  // fq + 4 u (u = 0, 1), as tile_mv8 leaves them
   const int lane = threadIdx.x & 63, fi = lane & 15, fq = lane >> 4;
   const int rr = 16 * (threadIdx.x >> 6) + fi;
-  cplx acc[2 * NG], xv[2 * NG];
+  cplx acc[2], xv[2];
 #pragma unroll
-  for (int u = 0; u < 2 * NG; ++u) {
+  for (int u = 0; u < 2; ++u) {
     const int rs = fq + 4 * u;
     acc[u] = (rr < nb && rs < nrhs) ? X[(o + rr) + (long)rs * ldx] : cmk(0, 0);
     xv[u] = cmk(0, 0);
@@ -233,17 +345,16 @@ __global__ __launch_bounds__(256) void trsv_kernel(int n, const T *LU, long ld, 
     }
   };
   bool ok = true;
-  // The B operand of group g from solved block k.  A solved block is published in
-  // the order its consumers read it: word (16 g + s) * 64 + l holds lane l's operand
-  // of step s (row 4 s + l / 16 % 4, right-hand side 8 g + l % 8, real part for
+  // The B operand from solved block k.  A solved block is published in the order its
+  // consumers read it: word s * 64 + l of the group's area holds lane l's operand
+  // of step s (row 4 s + l / 16 % 4, right-hand side l % 8, real part for
   // l % 16 < 8), so each load instruction of a wavefront reads 512 contiguous
   // bytes.  Waits until every word the lane uses is published (rows beyond a ragged
   // block and absent right-hand sides are zero).
-  auto poll = [&](int k, int g, double(&bz)[16]) {
-    const unsigned long long *zw =
-        (const unsigned long long *)(zbuf + (size_t)k * TS_NB * BM_MAX_NRHS) + (size_t)g * 16 * 64 + lane;
+  auto poll = [&](int k, double(&bz)[16]) {
+    const unsigned long long *zw = (const unsigned long long *)(zbuf + (size_t)k * TS_NB * BM_MAX_NRHS) + lane;
     const int kn = (n - k * TS_NB < TS_NB) ? n - k * TS_NB : TS_NB;
-    const bool colok = 8 * g + (fi & 7) < nrhs;
+    const bool colok = (fi & 7) < nrhs;
     unsigned long long v[16];
 #pragma unroll
     for (int s = 0; s < 16; ++s) v[s] = ld_agent(zw + 64 * s);
@@ -272,34 +383,24 @@ __global__ __launch_bounds__(256) void trsv_kernel(int n, const T *LU, long ld, 
     if (i < nd1 || i > nd1) {
       // acc -= M_bk x_k (a dependency but the last), or xv -= W_b x_k (the last one)
       const int k = (i < nd1) ? dep_block(i) : (LOWER ? b - 1 : b + 1);
-#pragma unroll
-      for (int g = 0; g < NG; ++g) {
-        if (8 * g < nrhs) {
-          double bz[16];
-          poll(k, g, bz);
-          if (i < nd1)
-            tile_mv8(tl, bz, acc[2 * g], acc[2 * g + 1], -1.0);
-          else
-            tile_mv8(tl, bz, xv[2 * g], xv[2 * g + 1], -1.0);
-        }
-      }
+      double bz[16];
+      poll(k, bz);
+      if (i < nd1)
+        tile_mv8(tl, bz, acc[0], acc[1], -1.0);
+      else
+        tile_mv8(tl, bz, xv[0], xv[1], -1.0);
     } else {
       // xv = inv(D_b) acc: the residual of the whole block goes through LDS
 #pragma unroll
-      for (int u = 0; u < 2 * NG; ++u) Z[rr][fq + 4 * u] = (rr < nb) ? acc[u] : cmk(0, 0);
+      for (int u = 0; u < 2; ++u) Z[rr][fq + 4 * u] = (rr < nb) ? acc[u] : cmk(0, 0);
       __syncthreads();
+      double bz[16];
 #pragma unroll
-      for (int g = 0; g < NG; ++g) {
-        if (8 * g < nrhs) {
-          double bz[16];
-#pragma unroll
-          for (int s = 0; s < 16; ++s) {
-            const cplx z = Z[4 * s + fq][8 * g + (fi & 7)];
-            bz[s] = (fi < 8) ? z.x : z.y;
-          }
-          tile_mv8(tl, bz, xv[2 * g], xv[2 * g + 1], 1.0);
-        }
+      for (int s = 0; s < 16; ++s) {
+        const cplx z = Z[4 * s + fq][fi & 7];
+        bz[s] = (fi < 8) ? z.x : z.y;
       }
+      tile_mv8(tl, bz, xv[0], xv[1], 1.0);
     }
   };
   // the next item's tile is loaded before the current item waits for its block
@@ -313,15 +414,15 @@ __global__ __launch_bounds__(256) void trsv_kernel(int n, const T *LU, long ld, 
       run_item(i + 1, tb);
     }
   }
-  // publication: row rr, right-hand side 8 g + c of the group -> words
-  // (16 g + rr / 4) * 64 + 16 (rr % 4) + c (+ 8 for the imaginary part)
+  // publication: row rr, right-hand side c of the group -> words
+  // (rr / 4) * 64 + 16 (rr % 4) + c (+ 8 for the imaginary part)
   unsigned long long *zo = (unsigned long long *)(zbuf + (size_t)b * TS_NB * BM_MAX_NRHS);
 #pragma unroll
-  for (int u = 0; u < 2 * NG; ++u) {
+  for (int u = 0; u < 2; ++u) {
     const int rs = fq + 4 * u;
     if (rs < nrhs && rr < nb) {
       X[(o + rr) + (long)rs * ldx] = xv[u];
-      unsigned long long *q = zo + (size_t)(16 * (u >> 1) + (rr >> 2)) * 64 + 16 * (rr & 3) + (rs & 7);
+      unsigned long long *q = zo + (size_t)(rr >> 2) * 64 + 16 * (rr & 3) + rs;
       st_agent(q, (unsigned long long)__double_as_longlong(xv[u].x));
       st_agent(q + 8, (unsigned long long)__double_as_longlong(xv[u].y));
     }
@@ -344,13 +445,13 @@ static int launch_trsv(hipStream_t s, bm_getrf_ws *w, int lower, int n, const T 
   const int nblk = (n + TS_NB - 1) / TS_NB;
   int32_t *ticket = (int32_t *)w->zbuf + (lower ? 0 : 1);
   cplx *zb = w->zbuf + 1 + (lower ? 0 : (size_t)nblk * TS_NB * BM_MAX_NRHS);
-  typedef void (*trsv_fn)(int, const T *, long, const cplx *, cplx *, long, int, int32_t *, cplx *, int32_t *);
-  static const trsv_fn fns[2][3] = {{trsv_kernel<false, 1, T>, trsv_kernel<false, 2, T>, trsv_kernel<false, 4, T>},
-                                    {trsv_kernel<true, 1, T>, trsv_kernel<true, 2, T>, trsv_kernel<true, 4, T>}};
-  const int gi = (nrhs <= 8) ? 0 : (nrhs <= 16) ? 1 : 2;
-  static_assert(BM_MAX_NRHS <= 32, "the triangular solves take at most four groups of eight right-hand sides");
-  hipLaunchKernelGGL(fns[lower ? 1 : 0][gi], dim3(nblk), dim3(256), 0, s, n, LU, (long)ld, dinv, X, (long)ldx, nrhs,
-                     ticket, zb, dev_err);
+  const dim3 grid(nblk * ((nrhs + 7) / 8));
+  if (lower)
+    hipLaunchKernelGGL((trsv_kernel<true, T>), grid, dim3(256), 0, s, n, LU, (long)ld, dinv, X, (long)ldx, nrhs, ticket,
+                       zb, dev_err);
+  else
+    hipLaunchKernelGGL((trsv_kernel<false, T>), grid, dim3(256), 0, s, n, LU, (long)ld, dinv, X, (long)ldx, nrhs, ticket,
+                       zb, dev_err);
   BM_HIP_TRY(hipGetLastError());
   return BM_OK;
 }
