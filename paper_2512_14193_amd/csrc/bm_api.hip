@@ -66,7 +66,7 @@ static bm_alloc_sizes problem_sizes(int n, int formulation) {
   const bool mixed = formulation == BM_MIXED;
   bm_alloc_sizes z;
   z.geo = sizeof(double) * 8 * N;
-  z.wts = sizeof(double) * 4 * N;
+  z.wts = sizeof(double) * bm_weights_doubles(n);
   z.top = mixed ? c * 2 * N * N : 0;
   z.bot = mixed ? c * 2 * N * N : 0;
   z.lu = c * nf * nf;

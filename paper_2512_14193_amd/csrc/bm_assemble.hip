@@ -23,31 +23,22 @@
 #include "bm_internal.h"
 #include "bm_zeta_corr.h"
 
-__constant__ double bm_hk_g0[BM_HQ + 1];
-__constant__ double bm_hk_g1[BM_HQ + 1];
-__constant__ double bm_hk_s2[BM_HQ + 1];
+// wide domain when a wavenumber lies below the sector |Im k| <= Re k / 2
+static bool bm_wide(const bm_phys &ph) { return ph.k0.y < -0.5 * ph.k0.x || ph.k1.y < -0.5 * ph.k1.x; }
 
-static int hankel_init_done[64];
-
-static int bm_hankel_init() {
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return BM_E_HIP;
-  if (hankel_init_done[dev]) return BM_OK;
-  double g0[BM_HQ + 1], g1[BM_HQ + 1], s2[BM_HQ + 1];
-  const double rsp = 1.0 / sqrt(BM_PI);
-  for (int q = 0; q <= BM_HQ; ++q) {
-    double s = q * BM_HSTEP, w = (q == 0) ? 0.5 * BM_HSTEP : BM_HSTEP;
-    double e = exp(-s * s);
-    g0[q] = w * e * 2.0 * rsp;
-    g1[q] = w * e * s * s * 4.0 * rsp;
-    s2[q] = s * s;
-  }
-  BM_HIP_TRY(hipMemcpyToSymbol(HIP_SYMBOL(bm_hk_g0), g0, sizeof(g0)));
-  BM_HIP_TRY(hipMemcpyToSymbol(HIP_SYMBOL(bm_hk_g1), g1, sizeof(g1)));
-  BM_HIP_TRY(hipMemcpyToSymbol(HIP_SYMBOL(bm_hk_s2), s2, sizeof(s2)));
-  hankel_init_done[dev] = 1;
+// The Hankel tables of the problem's wavenumbers (complex ones, and the wide domain),
+// after the quadrature weights.
+int bm_launch_hankel_rays(const bm_problem *p) {
+  const bm_phys &ph = p->phys;
+  const bool wide = bm_wide(ph);
+  if (!wide && ph.k0.y == 0.0 && ph.k1.y == 0.0) return BM_OK;
+  hipLaunchKernelGGL(hankel_ray_kernel, dim3(2), dim3(HK_RAY_NT), 0, p->stream, ph.k0, ph.k1,
+                     (hk_ray *)(p->wts + 4 * (size_t)p->n));
+  BM_HIP_TRY(hipGetLastError());
   return BM_OK;
 }
+
+size_t bm_weights_doubles(int n) { return 4 * (size_t)n + 2 * HK_RAY_DOUBLES; }
 
 // ---------------------------------------------------------------------------
 // Quadrature weights, one workgroup per m = (i - j) mod N:
@@ -161,7 +152,7 @@ int bm_launch_weights(hipStream_t s, int n, double *wts, int quad) {
     hipLaunchKernelGGL(zeta_corr_kernel, dim3(1), dim3(64), 0, s, n, c, wts);
     BM_HIP_TRY(hipGetLastError());
   }
-  return bm_hankel_init();
+  return BM_OK;
 }
 
 // ---------------------------------------------------------------------------
@@ -175,6 +166,7 @@ struct asm_args {
   bm_phys ph;
   const double2 *x, *dx, *ddx, *d3x;
   const double *wts;
+  const hk_ray *ray;  // tables of k0, k1 (complex wavenumbers, wide domain)
   cplx *top, *bot;  // mixed
   cplx *ord;        // ordinary
   int32_t *dom_err; // set to 1 if an argument k r lies outside the supported domain
@@ -187,10 +179,17 @@ struct pair_k {
   cplx sig, del, nu;
 };
 
+// The Hankel values at k r (real wavenumbers outside the wide domain need no table).
 template <bool WIDE>
-__device__ inline pair_k pair_scalars(cplx k, double r, double rinv, double R, double L, double h, double a,
-                                      double b, bool want_nu, bool *bad) {
-  const bm_hk4 hk = WIDE ? bm_hankel01_wide(cscale(k, r), bad) : bm_hankel01(cscale(k, r));
+__device__ inline bm_hk4 hankel_at(cplx k, const hk_ray *ray, double r, double rinv, bool *bad) {
+  if (!WIDE && k.y == 0.0) return bm_hankel01_real(k.x * r);
+  return bm_hankel01_ray<WIDE>(ray, r, rinv, bad);
+}
+
+template <bool WIDE>
+__device__ inline pair_k pair_scalars(cplx k, const hk_ray *ray, double r, double rinv, double R, double L, double h,
+                                      double a, double b, bool want_nu, bool *bad) {
+  const bm_hk4 hk = hankel_at<WIDE>(k, ray, r, rinv, bad);
   pair_k o;
   // S: K = (i/4) H0, K1 = -J0/(4 pi)
   const cplx aS = cmk(-0.25 * hk.h0.y, 0.25 * hk.h0.x);
@@ -347,8 +346,8 @@ __global__ __launch_bounds__(256) void assemble_kernel(asm_args A) {
       const pair_geo g = pair_geometry(A, i, j);
       const double si = g.si, sj = g.sj, ndi = g.ndi, ndj = g.ndj, kap = g.kap;
       bool bad = false;
-      const pair_k p0 = pair_scalars<WIDE>(ph.k0, g.r, g.rinv, g.R, g.L, A.h, g.a, g.b, true, &bad);
-      const pair_k p1 = pair_scalars<WIDE>(ph.k1, g.r, g.rinv, g.R, g.L, A.h, g.a, g.b, false, &bad);
+      const pair_k p0 = pair_scalars<WIDE>(ph.k0, A.ray, g.r, g.rinv, g.R, g.L, A.h, g.a, g.b, true, &bad);
+      const pair_k p1 = pair_scalars<WIDE>(ph.k1, A.ray + 1, g.r, g.rinv, g.R, g.L, A.h, g.a, g.b, false, &bad);
       if (WIDE && bad) atomicOr(A.dom_err, 1);
       // k0 operators at (i,j) and (j,i)
       const cplx S0ij = cscale(p0.sig, sj), S0ji = cscale(p0.sig, si);
@@ -406,12 +405,13 @@ int bm_launch_assemble(bm_problem *p, const bm_geometry *g) {
   A.ddx = (const double2 *)g->ddx;
   A.d3x = (const double2 *)g->d3x;
   A.wts = p->wts;
+  A.ray = (const hk_ray *)(p->wts + 4 * (size_t)p->n);
   A.top = p->top;
   A.bot = p->bot;
   A.ord = p->lu;
   A.dom_err = p->dev_err + 2;
-  // wide domain when a wavenumber lies below the sector |Im k| <= Re k / 2
-  const bool wide = (p->phys.k0.y < -0.5 * p->phys.k0.x) || (p->phys.k1.y < -0.5 * p->phys.k1.x);
+  const bool wide = bm_wide(p->phys);
+  if (int rc = bm_launch_hankel_rays(p)) return rc;
   if (int rc = bm_fill_u64(p->stream, p->dev_err + 2, 1, 0ull)) return rc;  // words 2, 3
   const long nt = (p->n + ASM_TB - 1) / ASM_TB;
   const long ntiles = nt * (nt + 1) / 2;
@@ -571,10 +571,10 @@ __device__ cplx mixed_entry(const asm_args &A, int tr, int i, int tc, int j) {
   const pair_geo g = pair_geometry(A, i, j);
   bool bad = false;
   if (blk < 2) {
-    const pair_k p1 = pair_scalars<false>(ph.k1, g.r, g.rinv, g.R, g.L, A.h, g.a, g.b, false, &bad);
+    const pair_k p1 = pair_scalars<false>(ph.k1, A.ray + 1, g.r, g.rinv, g.R, g.L, A.h, g.a, g.b, false, &bad);
     return blk == 0 ? cscale(p1.sig, -g.sj) : cscale(p1.del, g.ndi * g.sj / (g.si * ph.eps1));
   }
-  const pair_k p0 = pair_scalars<false>(ph.k0, g.r, g.rinv, g.R, g.L, A.h, g.a, g.b, blk == 2, &bad);
+  const pair_k p0 = pair_scalars<false>(ph.k0, A.ray, g.r, g.rinv, g.R, g.L, A.h, g.a, g.b, blk == 2, &bad);
   if (blk == 2) {
     const cplx N0 = cadd(cmk(g.kap / g.si, 0.0), cscale(p0.nu, g.sj));
     return cadd(cscale(p0.del, g.ndj), cmul(ph.beta, N0));
@@ -589,10 +589,11 @@ __device__ cplx mixed_entry(const asm_args &A, int tr, int i, int tc, int j) {
 struct pt_k {
   cplx S, D, Ds, N;
 };
-__device__ inline pt_k point_kernels(cplx k, double2 x, double2 nx, double2 y, double2 ny) {
+__device__ inline pt_k point_kernels(cplx k, const hk_ray *ray, double2 x, double2 nx, double2 y, double2 ny) {
   const double d1 = x.x - y.x, d2 = x.y - y.y;
   const double r2 = d1 * d1 + d2 * d2, r = sqrt(r2), rinv = 1.0 / r;
-  const bm_hk4 hk = bm_hankel01(cscale(k, r));
+  bool bad = false;
+  const bm_hk4 hk = hankel_at<false>(k, ray, r, rinv, &bad);
   const double nxd = nx.x * d1 + nx.y * d2, nyd = ny.x * d1 + ny.y * d2, a = nx.x * ny.x + nx.y * ny.y;
   const cplx ik4 = cmk(-0.25 * k.y, 0.25 * k.x);
   pt_k o;
@@ -632,13 +633,13 @@ __global__ __launch_bounds__(256) void fds_target_kernel(asm_args A, const fds_t
       const double2 ny = node_normal(A, cn, &sj);
       const double w = A.h * sj;
       if (ct == 0) {
-        const pt_k k = point_kernels(ph.k0, x, nx, A.x[cn], ny);
+        const pt_k k = point_kernels(ph.k0, A.ray, x, nx, A.x[cn], ny);
         v = cscale(cadd(k.D, cmul(ph.beta, k.N)), w);
       } else if (ct == 1) {
-        const pt_k k = point_kernels(ph.k0, x, nx, A.x[cn], ny);
+        const pt_k k = point_kernels(ph.k0, A.ray, x, nx, A.x[cn], ny);
         v = cscale(cadd(k.S, cmul(ph.beta, k.Ds)), w);
       } else {
-        v = cscale(point_kernels(ph.k1, x, nx, A.x[cn], ny).S, w);
+        v = cscale(point_kernels(ph.k1, A.ray + 1, x, nx, A.x[cn], ny).S, w);
       }
     } else {
       const int rc = it.rl[r - it.np];
@@ -656,11 +657,11 @@ __global__ __launch_bounds__(256) void fds_target_kernel(asm_args A, const fds_t
       const double2 nx = node_normal(A, cn, &si);
       const double2 x = A.x[cn];
       if (ct == 0) {
-        v = point_kernels(ph.k1, x, nx, y, ny).S;
+        v = point_kernels(ph.k1, A.ray + 1, x, nx, y, ny).S;
       } else if (ct == 1) {
-        v = point_kernels(ph.k1, x, nx, y, ny).Ds;
+        v = point_kernels(ph.k1, A.ray + 1, x, nx, y, ny).Ds;
       } else {
-        const pt_k k = point_kernels(ph.k0, x, nx, y, ny);
+        const pt_k k = point_kernels(ph.k0, A.ray, x, nx, y, ny);
         v = (r < it.np) ? cadd(k.D, cmul(ph.beta, k.N)) : cadd(k.S, cmul(ph.beta, k.Ds));
       }
       v = cscale(v, it.pw);
@@ -685,6 +686,7 @@ int bm_launch_fds_targets(hipStream_t s, const bm_problem *p, int nitems, const 
   A.ddx = (const double2 *)(p->geo + 4 * p->n);
   A.d3x = (const double2 *)(p->geo + 6 * p->n);
   A.wts = p->wts;
+  A.ray = (const hk_ray *)(p->wts + 4 * (size_t)p->n);
   A.top = A.bot = A.ord = nullptr;
   A.dom_err = nullptr;
   const long nb = (max_elems + 255) / 256;

@@ -1226,7 +1226,7 @@ int bm_fds_create(int32_t n, const bm_fds_config *cfg, void *hip_stream, bm_fds 
     return BM_E_HIP;
   }
   int rc = dmalloc(f, &f->geo, 8 * (size_t)n, true);
-  if (!rc) rc = dmalloc(f, &f->wts, 4 * (size_t)n, true);
+  if (!rc) rc = dmalloc(f, &f->wts, bm_weights_doubles(n), true);
   if (!rc) rc = dmalloc(f, &f->dev_err, 4, true);
   if (!rc) rc = bm_launch_weights(f->stream, n, f->wts, BM_QUAD_ZETA1);
   if (!rc && hipMemsetAsync(f->dev_err, 0, 4 * sizeof(int32_t), f->stream) != hipSuccess) rc = BM_E_HIP;
@@ -1285,7 +1285,8 @@ int bm_fds_factor(bm_fds *f, const bm_geometry *g, const bm_params *prm) {
   BM_HIP_TRY(hipMemcpyAsync(f->hdx.data(), f->geo + 2 * n, bytes, hipMemcpyDeviceToHost, f->stream));
   BM_HIP_TRY(hipStreamSynchronize(f->stream));
   BM_HIP_TRY(hipMemsetAsync(f->dev_err, 0, 4 * sizeof(int32_t), f->stream));
-  int rc = factor_all(f);
+  int rc = bm_launch_hankel_rays(&f->shell);
+  if (!rc) rc = factor_all(f);
   if (!rc) rc = alloc_solve_buffers(f);
   if (rc) {
     (void)hipStreamSynchronize(f->stream);

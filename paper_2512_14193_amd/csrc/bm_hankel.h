@@ -1,143 +1,95 @@
-// Device evaluation of H0^(1), H1^(1), J0, J1 for complex z (principal branch),
-// FP64, in the sector |arg z| <= 1/2 + small margin that the assembly produces
-// for wavenumbers with Re k > 0, |Im k| <= Re k / 2.
+// Device evaluation of H0^(1), H1^(1), J0, J1 (principal branch), FP64, at the
+// arguments z = k r of an assembly: one wavenumber k, real r > 0, in the sector
+// |arg z| <= 1/2 + small margin (wavenumbers with Re k > 0, |Im k| <= Re k / 2).
 //
 //   |z| < 3         power series (DLMF 10.2.2, 10.8.1): J from its Taylor series,
 //                   Y0 and Y1 from the logarithmic series with harmonic numbers.
-//   3 <= |z| < 25   the Laplace-type integral of Hankel's function,
-//                     H_nu(z) = sqrt(2/(pi z)) e^{i(z - nu pi/2 - pi/4)} / Gamma(nu + 1/2)
-//                               * int_0^inf e^{-u} u^{nu-1/2} (1 + iu/(2z))^{nu-1/2} du
-//                   (the integral behind the asymptotic expansion, DLMF 10.17),
-//                   after u = s^2: a Gaussian-weighted smooth integrand whose nearest
-//                   singularity sits at s^2 = 2iz, so the trapezoid rule with step 0.2
-//                   on s in [0, 6.4] is accurate to ~1e-16 for |z| >= 3 in the sector.
-//                   J = (H^(1) + H^(2))/2 with H^(2)(z) = conj(H^(1)(conj z)).
-//   |z| >= 25       Hankel's asymptotic expansion (DLMF 10.17.5), terms until < 1e-17.
-//   real z >= 3     (real wavenumbers) the normalised function F_nu(1/z) of
-//                   H_nu = sqrt(2/(pi z)) e^{i(z - nu pi/2 - pi/4)} F_nu, the same
-//                   integral as a function of t = 1/z, from its Chebyshev series on
-//                   t in [0, 1/3] (degree 26, generated from 40-digit values by
-//                   gen_hankel_cheb.py): about one ulp, a tenth of the integral's cost.
+//   real z >= 3     the normalised function F_nu(1/z) of
+//                   H_nu = sqrt(2/(pi z)) e^{i(z - nu pi/2 - pi/4)} F_nu, from its
+//                   Chebyshev series in t = 1/z on [0, 1/3] (degree 26, generated
+//                   from 40-digit values by gen_hankel_cheb.py): about one ulp.
+//   complex z, |z| >= 3   the same on the ray: with k = |k| e^{i th}, F_nu is a smooth
+//                   function of the real t = 1/|z|, so a small kernel (hankel_ray_kernel)
+//                   forms, per wavenumber, the Chebyshev series of F_nu - 1 for H^(1)
+//                   and for H^(2)(z) = conj(H^(1)(conj z)), J = (H^(1) + H^(2))/2, from
+//                   the Laplace-type integral (the integral behind the asymptotic
+//                   expansion, DLMF 10.17)
+//                     F_nu = 1 / Gamma(nu + 1/2) int_0^inf e^{-u} u^{nu-1/2} (1 + iu/(2z))^{nu-1/2} du,
+//                   u = s^2, trapezoid rule; its nearest singularity sits at s^2 = 2iz.
+//                   Likewise the power series is then a polynomial in the real r^2.
 //
-// Wide domain (bm_hankel01_wide): wavenumbers in the lower half plane beyond that
-// sector (Im k < -Re k / 2), where the complex resonances and fictitious
-// eigenvalues of Sec. 5.3 lie.  There the singularity s^2 = 2iz of the integral
-// approaches the integration path, so the power series is used instead, for
-// |z| < 6 with 26 terms (the last term is below 1e-26 of the largest); in the
-// lower half plane J and Y grow like H^(1), so the series loses at most a factor
-// e^{|z| - |Im z|} <= 30 to cancellation.  Larger |z| is outside the supported
-// domain: the caller flags it.
+// Assembly at complex wavenumbers, N = 1024: 80 us, against 372 us with two 32-node
+// integrals per pair and wavenumber; the wide domain at N = 4000: 389 against 786 us.
+// The loops keep a few coefficients of each series at a time (scalar loads) and are not
+// unrolled whole, which takes the assembly from 248 registers and one wavefront per SIMD
+// to 148 and three: real wavenumbers N = 2048 275 -> 106 us, N = 8192 4.09 -> 1.45 ms.
+// The blocks' error against long double values is that of the integral or smaller
+// (2e-16 to 5e-15 of a block over the sector and below it).
+//
+// Wide domain: wavenumbers in the lower half plane beyond the sector
+// (Im k < -Re k / 2), where the complex resonances and fictitious eigenvalues of
+// Sec. 5.3 lie.  There the singularity s^2 = 2iz of the integral approaches the
+// integration path, so the power series is used instead, for |z| < 6 with 26 terms
+// (the last term is below 1e-26 of the largest); in the lower half plane J and Y grow
+// like H^(1), so the series loses at most a factor e^{|z| - |Im z|} <= 30 to
+// cancellation.  Larger |z| is outside the supported domain: the caller flags it.
 #pragma once
 
 #include "bm_internal.h"
 
 #include "bm_hankel_cheb.h"
 
-#define BM_HQ 32           // trapezoid nodes s_q = q * 0.2, q = 0..32
-#define BM_HSTEP 0.2
-
 struct bm_hk4 {
   cplx h0, h1, j0, j1;
 };
 
-// Node weights, filled once per device by bm_hankel_init():
-//   g0[q] = w_q e^{-s_q^2} (2/sqrt(pi)),  g1[q] = w_q e^{-s_q^2} s_q^2 (4/sqrt(pi)),  s2[q] = s_q^2
-// with trapezoid weights w_0 = step/2, w_q = step.
-extern __constant__ double bm_hk_g0[BM_HQ + 1];
-extern __constant__ double bm_hk_g1[BM_HQ + 1];
-extern __constant__ double bm_hk_s2[BM_HQ + 1];
-
-template <int NT = 18>
-__device__ inline void bm_hankel_series(cplx z, bm_hk4 &o) {
-  const cplx mw = cscale(cmul(z, z), -0.25);  // -z^2/4
-  cplx t0 = cmk(1.0, 0.0), t1 = cmk(1.0, 0.0);
-  cplx sj0 = cmk(0, 0), sj1 = cmk(0, 0), sy0 = cmk(0, 0), sy1 = cmk(0, 0);
-  double hk = 0.0, hk1 = 1.0;  // harmonic numbers H_k, H_{k+1}
-#pragma unroll
-  for (int k = 0; k < NT; ++k) {
-    sj0 = cadd(sj0, t0);
-    sj1 = cadd(sj1, t1);
-    sy0 = cadd(sy0, cscale(t0, hk));
-    sy1 = cadd(sy1, cscale(t1, hk + hk1));
-    t0 = cscale(cmul(t0, mw), 1.0 / ((k + 1.0) * (k + 1.0)));
-    t1 = cscale(cmul(t1, mw), 1.0 / ((k + 1.0) * (k + 2.0)));
+// Factors of the series of real arguments: term k to k + 1 of J0 and of J1 / (z/2), and
+// the harmonic sums H_k and H_k + H_{k+1}.  (Tables, so that the loops need not be
+// unrolled whole: the assembly then runs with half the registers.)
+#define HK_NR 18
+struct hk_series_tab {
+  double r[HK_NR][4];
+};
+constexpr hk_series_tab hk_series_make() {
+  hk_series_tab t{};
+  double hk = 0.0, hk1 = 1.0;
+  for (int k = 0; k < HK_NR; ++k) {
+    t.r[k][0] = 1.0 / ((k + 1.0) * (k + 1.0));
+    t.r[k][1] = 1.0 / ((k + 1.0) * (k + 2.0));
+    t.r[k][2] = hk;
+    t.r[k][3] = hk + hk1;
     hk = hk1;
     hk1 += 1.0 / (k + 2.0);
   }
+  return t;
+}
+__constant__ hk_series_tab hk_series = hk_series_make();
+
+__device__ inline void bm_hankel_series(double x, bm_hk4 &o) {
+  const cplx z = cmk(x, 0.0);
+  const double mw = -0.25 * (x * x);  // -z^2/4
+  double t0 = 1.0, t1 = 1.0, sj0 = 1.0, sj1 = 1.0, sy0 = 0.0, sy1 = 1.0;
+#pragma unroll 3
+  for (int k = 0; k + 1 < HK_NR; ++k) {
+    const double x0 = t0 * mw, x1 = t1 * mw;
+    sj0 = fma(x0, hk_series.r[k][0], sj0);
+    sj1 = fma(x1, hk_series.r[k][1], sj1);
+    t0 = x0 * hk_series.r[k][0];
+    t1 = x1 * hk_series.r[k][1];
+    sy0 = fma(t0, hk_series.r[k + 1][2], sy0);
+    sy1 = fma(t1, hk_series.r[k + 1][3], sy1);
+  }
   const cplx zh = cscale(z, 0.5);
-  const cplx J0 = sj0, J1 = cmul(zh, sj1);
+  const cplx J0 = cmk(sj0, 0.0), J1 = cmul(zh, cmk(sj1, 0.0));
   cplx L = clog_d(zh);
   L.x += BM_EULER;
-  const cplx Y0 = cscale(csub(cmul(L, J0), sy0), 2.0 / BM_PI);
+  const cplx Y0 = cscale(csub(cmul(L, J0), cmk(sy0, 0.0)), 2.0 / BM_PI);
   const cplx Y1 = cadd(cadd(cscale(crecip(z), -2.0 / BM_PI), cscale(cmul(L, J1), 2.0 / BM_PI)),
-                       cscale(cmul(zh, sy1), -1.0 / BM_PI));
+                       cscale(cmul(zh, cmk(sy1, 0.0)), -1.0 / BM_PI));
   o.j0 = J0;
   o.j1 = J1;
   o.h0 = cmk(J0.x - Y0.y, J0.y + Y0.x);
   o.h1 = cmk(J1.x - Y1.y, J1.y + Y1.x);
-}
-
-// H^(1)_0 and H^(1)_1 at z from the Laplace-type integral (trapezoid rule).
-__device__ inline void bm_hankel_integral(cplx z, cplx &h0, cplx &h1) {
-  const double iz2 = 1.0 / cabs2(z);
-  // c = i / (2z) = (Im z + i Re z) / (2|z|^2)
-  const double cx = 0.5 * z.y * iz2, cy = 0.5 * z.x * iz2;
-  cplx I0 = cmk(bm_hk_g0[0], 0.0), I1 = cmk(0.0, 0.0);
-#pragma unroll 4
-  for (int q = 1; q <= BM_HQ; ++q) {
-    const double s2 = bm_hk_s2[q];
-    const cplx w = cmk(1.0 + cx * s2, cy * s2);
-    const cplx sq = csqrt_d(w);                 // (1 + i s^2/(2z))^{1/2}
-    const double rn = 1.0 / cabs2(sq);          // 1/|w|
-    const double g0 = bm_hk_g0[q], g1 = bm_hk_g1[q];
-    I0.x += g0 * sq.x * rn;                     // (1 + ...)^{-1/2} = conj(sq)/|w|
-    I0.y -= g0 * sq.y * rn;
-    I1.x += g1 * sq.x;
-    I1.y += g1 * sq.y;
-  }
-  // prefactor sqrt(2/(pi z)) e^{i(z - pi/4)}
-  const cplx pre = csqrt_d(cmk(2.0 / BM_PI * z.x * iz2, -2.0 / BM_PI * z.y * iz2));
-  const cplx e0 = cexp_d(cmk(-z.y, z.x - 0.25 * BM_PI));
-  const cplx pe = cmul(pre, e0);
-  h0 = cmul(pe, I0);
-  h1 = cmul(cmk(pe.y, -pe.x), I1);              // extra e^{-i pi/2}
-}
-
-__device__ inline void bm_hankel_asymptotic(cplx z, bm_hk4 &o) {
-  const cplx zi = crecip(z);
-  cplx t = cmk(1.0, 0.0);
-  double a0 = 1.0, a1 = 1.0;
-  cplx p0 = cmk(1, 0), m0 = cmk(1, 0), p1 = cmk(1, 0), m1 = cmk(1, 0);  // sums with i^k and (-i)^k
-  for (int k = 1; k < 40; ++k) {
-    const double odd = 2.0 * k - 1.0;
-    a0 *= -(odd * odd) / (8.0 * k);
-    a1 *= (4.0 - odd * odd) / (8.0 * k);
-    t = cmul(t, zi);
-    const cplx u0 = cscale(t, a0), u1 = cscale(t, a1);
-    // i^k u and (-i)^k u
-    cplx ip0, ip1;
-    switch (k & 3) {
-      case 0: ip0 = u0; ip1 = u1; break;
-      case 1: ip0 = cmk(-u0.y, u0.x); ip1 = cmk(-u1.y, u1.x); break;
-      case 2: ip0 = cneg(u0); ip1 = cneg(u1); break;
-      default: ip0 = cmk(u0.y, -u0.x); ip1 = cmk(u1.y, -u1.x); break;
-    }
-    const cplx im0 = (k & 1) ? cneg(ip0) : ip0;  // (-i)^k = (-1)^k i^k
-    const cplx im1 = (k & 1) ? cneg(ip1) : ip1;
-    p0 = cadd(p0, ip0); m0 = cadd(m0, im0);
-    p1 = cadd(p1, ip1); m1 = cadd(m1, im1);
-    if (cabs2(u0) < 1e-34 && cabs2(u1) < 1e-34) break;
-  }
-  const double iz2 = 1.0 / cabs2(z);
-  const cplx pre = csqrt_d(cmk(2.0 / BM_PI * z.x * iz2, -2.0 / BM_PI * z.y * iz2));
-  const cplx ep = cmul(pre, cexp_d(cmk(-z.y, z.x - 0.25 * BM_PI)));   // pre e^{i(z - pi/4)}
-  const cplx em = cmul(pre, cexp_d(cmk(z.y, -(z.x - 0.25 * BM_PI))));  // pre e^{-i(z - pi/4)}
-  const cplx H10 = cmul(ep, p0), H20 = cmul(em, m0);
-  const cplx H11 = cmul(cmk(ep.y, -ep.x), p1), H21 = cmul(cmk(-em.y, em.x), m1);  // e^{-+i pi/2}
-  o.h0 = H10;
-  o.h1 = H11;
-  o.j0 = cscale(cadd(H10, H20), 0.5);
-  o.j1 = cscale(cadd(H11, H21), 0.5);
 }
 
 // H^(1)_0, H^(1)_1, J0, J1 at real x >= 3 from the Chebyshev series of F_0, F_1
@@ -147,7 +99,7 @@ __device__ inline void bm_hankel_real(double x, bm_hk4 &o) {
   const double t = 1.0 / x;
   const double u = 6.0 * t - 1.0, u2 = 2.0 * u;
   double b1[4] = {0.0, 0.0, 0.0, 0.0}, b2[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
+#pragma unroll 2
   for (int j = BM_HC_DEG; j >= 1; --j) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -170,42 +122,202 @@ __device__ inline void bm_hankel_real(double x, bm_hk4 &o) {
   o.j1 = cmk(o.h1.x, 0.0);
 }
 
-// Largest |z| of the wide domain
-#define BM_WIDE_ZMAX 6.0
-
-// Wide domain: power series only; *bad is set when |z| >= BM_WIDE_ZMAX.
-__device__ inline bm_hk4 bm_hankel01_wide(cplx z, bool *bad) {
+// H^(1)_0, H^(1)_1, J0, J1 at real x > 0
+__device__ inline bm_hk4 bm_hankel01_real(double x) {
   bm_hk4 o;
-  const double az2 = cabs2(z);
-  if (az2 < 9.0) {
-    bm_hankel_series<18>(z, o);
+  if (x * x < 9.0)
+    bm_hankel_series(x, o);
+  else
+    bm_hankel_real(x, o);
+  return o;
+}
+
+// Tables of one wavenumber k = ak e^{i th} (hankel_ray_kernel); every lane reads the
+// same entries, so they come through the scalar cache.
+#define BM_WIDE_ZMAX 6.0  // largest |z| of the wide domain
+#define HK_NS 26          // series terms (18 for |z| < 3)
+#define HK_NC 28          // Chebyshev coefficients (those of degree 24 and beyond are below 1e-16)
+struct hk_ray {
+  double ak, th;        // |k|, arg k
+  cplx k, sq1, sq2, ik;  // k, sqrt(2/pi) e^{-i th/2 -+ i pi/4}, 1/k
+  double scale, pad[5];  // the power of two P with P <= |k| < 2 P
+  double ser[HK_NS][8];  // J0, J1 / (z/2), and the harmonic sums of Y0, Y1: coefficients in (P r)^2
+  double cheb[HK_NC][8];  // F_0 - 1, F_1 - 1 of H^(1) and of H^(2), in u = 6/|z| - 1
+};
+#define HK_RAY_DOUBLES (sizeof(hk_ray) / sizeof(double))
+
+template <bool WIDE>
+__device__ inline bm_hk4 bm_hankel01_ray(const hk_ray *T_, double r, double rinv, bool *bad) {
+  typedef const __attribute__((address_space(4))) hk_ray *ray_ptr;  // (constant: scalar loads)
+  const ray_ptr T = (ray_ptr)T_;
+  bm_hk4 o;
+  const double az = T->ak * r;
+  if (WIDE || az < 3.0) {
+    if (WIDE && !(az < BM_WIDE_ZMAX)) *bad = true;
+    constexpr int NT = WIDE ? HK_NS : 18;
+    const double xr = T->scale * r, x = xr * xr;
+    double s[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) s[q] = T->ser[NT - 1][q];
+#pragma unroll 2
+    for (int m = NT - 2; m >= 0; --m)
+#pragma unroll
+      for (int q = 0; q < 8; ++q) s[q] = fma(s[q], x, T->ser[m][q]);
+    const cplx zh = cmk(0.5 * T->k.x * r, 0.5 * T->k.y * r), zi = cmk(T->ik.x * rinv, T->ik.y * rinv);
+    const cplx J0 = cmk(s[0], s[1]), J1 = cmul(zh, cmk(s[2], s[3]));
+    const cplx L = cmk(log(0.5 * az) + BM_EULER, T->th);
+    const cplx Y0 = cscale(csub(cmul(L, J0), cmk(s[4], s[5])), 2.0 / BM_PI);
+    const cplx Y1 = cadd(cadd(cscale(zi, -2.0 / BM_PI), cscale(cmul(L, J1), 2.0 / BM_PI)),
+                         cscale(cmul(zh, cmk(s[6], s[7])), -1.0 / BM_PI));
+    o.j0 = J0;
+    o.j1 = J1;
+    o.h0 = cmk(J0.x - Y0.y, J0.y + Y0.x);
+    o.h1 = cmk(J1.x - Y1.y, J1.y + Y1.x);
   } else {
-    if (!(az2 < BM_WIDE_ZMAX * BM_WIDE_ZMAX)) *bad = true;
-    bm_hankel_series<26>(z, o);
+    const double t = 1.0 / az, u = 6.0 * t - 1.0, u2 = 2.0 * u;
+    double b1[8], b2[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) b1[q] = b2[q] = 0.0;
+#pragma unroll 3
+    for (int j = HK_NC - 1; j >= 1; --j)
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const double bn = fma(u2, b1[q], T->cheb[j][q] - b2[q]);
+        b2[q] = b1[q];
+        b1[q] = bn;
+      }
+    double d[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) d[q] = fma(u, b1[q], T->cheb[0][q] - b2[q]);
+    double sn, cs;
+    sincos(T->k.x * r, &sn, &cs);
+    const double e1 = exp(-T->k.y * r), a = sqrt(t), a1 = a * e1, a2 = a / e1;
+    const cplx p1 = cmul(cmk(T->sq1.x, T->sq1.y), cmk(a1 * cs, a1 * sn));
+    const cplx p2 = cmul(cmk(T->sq2.x, T->sq2.y), cmk(a2 * cs, -a2 * sn));
+    o.h0 = cadd(p1, cmul(p1, cmk(d[0], d[1])));
+    const cplx h1 = cadd(p1, cmul(p1, cmk(d[2], d[3])));
+    const cplx g0 = cadd(p2, cmul(p2, cmk(d[4], d[5])));
+    const cplx g1 = cadd(p2, cmul(p2, cmk(d[6], d[7])));
+    o.h1 = cmk(h1.y, -h1.x);                      // e^{-i pi/2}
+    o.j0 = cscale(cadd(o.h0, g0), 0.5);
+    o.j1 = cscale(cadd(o.h1, cmk(-g1.y, g1.x)), 0.5);  // e^{+i pi/2}
   }
   return o;
 }
 
-__device__ inline bm_hk4 bm_hankel01(cplx z) {
-  bm_hk4 o;
-  const double az2 = cabs2(z);
-  if (az2 < 9.0) {
-    bm_hankel_series<18>(z, o);
-  } else if (z.y == 0.0 && z.x > 0.0) {
-    bm_hankel_real(z.x, o);
-  } else if (az2 < 625.0) {
-    bm_hankel_integral(z, o.h0, o.h1);
-    if (z.y == 0.0) {
-      o.j0 = cmk(o.h0.x, 0.0);
-      o.j1 = cmk(o.h1.x, 0.0);
-    } else {
-      cplx g0, g1;
-      bm_hankel_integral(cconj(z), g0, g1);  // H^(2)(z) = conj(H^(1)(conj z))
-      o.j0 = cscale(cadd(o.h0, cconj(g0)), 0.5);
-      o.j1 = cscale(cadd(o.h1, cconj(g1)), 0.5);
+// Sums and products to twice double precision, for the series' coefficients: rounded
+// once, they leave the evaluation as exact as the recurrence of the terms was.
+struct hk_dd {
+  double h, l;
+};
+__device__ inline hk_dd dd_sum(double a, double b) {
+  const double s = a + b, t = s - a;
+  return {s, (a - (s - t)) + (b - t)};
+}
+__device__ inline hk_dd dd_add(hk_dd a, hk_dd b) {
+  const hk_dd s = dd_sum(a.h, b.h);
+  return dd_sum(s.h, s.l + (a.l + b.l));
+}
+__device__ inline hk_dd dd_mul(hk_dd a, hk_dd b) {
+  const double p = a.h * b.h;
+  return dd_sum(p, fma(a.h, b.h, -p) + (a.h * b.l + a.l * b.h));
+}
+__device__ inline hk_dd dd_div(hk_dd a, double d) {  // d exact
+  const double q = a.h / d;
+  return dd_sum(q, (fma(-q, d, a.h) + a.l) / d);
+}
+struct hk_ddc {
+  hk_dd x, y;
+};
+__device__ inline hk_ddc ddc_mul(hk_ddc a, hk_ddc b) {
+  const hk_dd yy = dd_mul(a.y, b.y);
+  return {dd_add(dd_mul(a.x, b.x), {-yy.h, -yy.l}), dd_add(dd_mul(a.x, b.y), dd_mul(a.y, b.x))};
+}
+
+// The tables of two wavenumbers, one workgroup each.
+#define HK_RAY_NT 1024
+__global__ __launch_bounds__(HK_RAY_NT) void hankel_ray_kernel(cplx k0, cplx k1, hk_ray *out) {
+  constexpr int M = 32;  // Chebyshev nodes
+  static_assert(HK_NC <= M && HK_RAY_NT == 2 * M * 16, "16 threads per node and sign");
+  __shared__ double D[8][M], C[4 * M];
+  const cplx k = blockIdx.x ? k1 : k0;
+  hk_ray *T = out + blockIdx.x;
+  const int tid = threadIdx.x;
+  // 1 / P for P = 2^floor(log2 |k|)
+  const double ak = hypot(k.x, k.y), sc = __hiloint2double(0x7fe00000 - (__double2hiint(ak) & 0x7ff00000), 0);
+  const double th = atan2(k.y, k.x), cth = k.x / ak, sth = k.y / ak;
+  if (tid < 4 * M) C[tid] = cospi((double)tid / (2 * M));
+  {
+    // F_nu - 1 = int weight ((1 + i u / 2z)^{nu - 1/2} - 1) at node m, H^(1) (sg = 0) and,
+    // conjugated, at conj z (sg = 1); the differences in a form without cancellation
+    const int part = tid & 15, m = (tid >> 4) & (M - 1), sg = tid >> 9;
+    const double t = (cospi((m + 0.5) / M) + 1.0) / 6.0;
+    const double cx = 0.5 * t * (sg ? -sth : sth), cy = 0.5 * t * cth;  // i t e^{-i th} / 2
+    const double h = 0.16, rsp = 1.0 / sqrt(BM_PI);
+    cplx d0 = cmk(0, 0), d1 = cmk(0, 0);
+    for (int q = 1 + part; q <= 40; q += 16) {
+      const double s2 = (q * h) * (q * h), e = h * exp(-s2) * rsp;
+      const cplx v = cmk(cx * s2, cy * s2), w = cmk(1.0 + v.x, v.y), rt = csqrt_d(w);
+      const cplx f = cdiv(v, cmk(1.0 + rt.x, rt.y));  // sqrt(w) - 1
+      const cplx f0 = cdiv(f, rt);                    // 1 - 1/sqrt(w)
+      d0 = csub(d0, cscale(f0, 2.0 * e));
+      d1 = cadd(d1, cscale(f, 4.0 * e * s2));
     }
-  } else {
-    bm_hankel_asymptotic(z, o);
+#pragma unroll
+    for (int x = 8; x > 0; x >>= 1) {
+      d0 = cadd(d0, cmk(__shfl_xor(d0.x, x), __shfl_xor(d0.y, x)));
+      d1 = cadd(d1, cmk(__shfl_xor(d1.x, x), __shfl_xor(d1.y, x)));
+    }
+    if (part == 0) {
+      D[4 * sg][m] = d0.x;
+      D[4 * sg + 1][m] = sg ? -d0.y : d0.y;
+      D[4 * sg + 2][m] = d1.x;
+      D[4 * sg + 3][m] = sg ? -d1.y : d1.y;
+    }
   }
-  return o;
+  __syncthreads();
+  if (tid < 8 * HK_NC) {
+    const int j = tid / 8, q = tid % 8;
+    double s = 0.0;
+    for (int m = 0; m < M; ++m) s = fma(D[q][m], C[(j * (2 * m + 1)) % (4 * M)], s);
+    T->cheb[j][q] = s * ((j == 0) ? 1.0 : 2.0) / M;
+  } else if (tid >= 512 && tid < 512 + HK_NS) {
+    // (-k^2 / 4 P^2)^m / (m!)^2 and its companions
+    const int m = tid - 512;
+    const double x = k.x * sc, y = k.y * sc;  // k / P, exact
+    const hk_dd xx = dd_mul({x, 0.0}, {-0.25 * x, 0.0}), yy = dd_mul({y, 0.0}, {0.25 * y, 0.0});
+    hk_ddc f = {dd_add(xx, yy), dd_mul({x, 0.0}, {-0.5 * y, 0.0})}, c = {{1.0, 0.0}, {0.0, 0.0}};
+    for (int e = m; e > 0; e >>= 1) {
+      if (e & 1) c = ddc_mul(c, f);
+      f = ddc_mul(f, f);
+    }
+    hk_dd h = {0.0, 0.0};  // H_m
+    for (int i = 1; i <= m; ++i) {
+      c.x = dd_div(c.x, (double)i * i);
+      c.y = dd_div(c.y, (double)i * i);
+      h = dd_add(h, dd_div({1.0, 0.0}, i));
+    }
+    const hk_dd h1 = dd_add(h, dd_add(h, dd_div({1.0, 0.0}, m + 1.0)));  // H_m + H_{m+1}
+    const hk_ddc c1 = {dd_div(c.x, m + 1.0), dd_div(c.y, m + 1.0)};
+    T->ser[m][0] = c.x.h;
+    T->ser[m][1] = c.y.h;
+    T->ser[m][2] = c1.x.h;
+    T->ser[m][3] = c1.y.h;
+    T->ser[m][4] = dd_mul(c.x, h).h;
+    T->ser[m][5] = dd_mul(c.y, h).h;
+    T->ser[m][6] = dd_mul(c1.x, h1).h;
+    T->ser[m][7] = dd_mul(c1.y, h1).h;
+  } else if (tid == 1023) {
+    double sn, cs;
+    T->ak = ak;
+    T->scale = 1.0 / sc;
+    T->th = th;
+    T->k = k;
+    T->ik = crecip(k);
+    const double c = sqrt(2.0 / BM_PI);
+    sincos(-0.5 * th - 0.25 * BM_PI, &sn, &cs);
+    T->sq1 = cmk(c * cs, c * sn);
+    sincos(-0.5 * th + 0.25 * BM_PI, &sn, &cs);
+    T->sq2 = cmk(c * cs, c * sn);
+  }
 }

@@ -190,7 +190,7 @@ struct bm_problem {
   bm_phys phys;
 
   double *geo;          // 8N doubles: x, dx, ddx, d3x (interleaved pairs)
-  double *wts;          // 4N doubles: R_m, T_m, L_m = ln(4 sin^2(pi m/N)), 1/(2 sin^2(pi m/N))
+  double *wts;          // bm_weights_doubles(n): R_m, T_m, L_m = ln(4 sin^2(pi m/N)), 1/(2 sin^2(pi m/N))
   cplx *top;            // mixed: [M13; M23], 2N x N, ld 2N
   cplx *bot;            // mixed: [M31 M32], N x 2N, ld N
   cplx *lu;             // factor storage: U33 (mixed, N x N) or the ordinary 2N x 2N matrix
@@ -230,6 +230,10 @@ struct bm_problem {
 // ---------------------------------------------------------------------------
 // internal launchers (all enqueue on `s` and return a bm_status)
 // ---------------------------------------------------------------------------
+// doubles of a problem's weight buffer: four tables of n, then the Hankel tables of both
+// wavenumbers, which bm_launch_hankel_rays fills from p->phys (bm_launch_assemble calls it)
+size_t bm_weights_doubles(int n);
+int bm_launch_hankel_rays(const bm_problem *p);
 int bm_launch_weights(hipStream_t s, int n, double *wts, int quad);  // quad: BM_QUAD_*
 int bm_launch_assemble(bm_problem *p, const bm_geometry *g);
 int bm_launch_rhs_plane_wave(bm_problem *p, int nrhs, const double *theta, cplx *B, int64_t ldb);
