@@ -16,8 +16,15 @@
 // Re += Ar Br - Ai Bi, Im += Ar Bi + Ai Br, four workgroups per CU.  For deep
 // ones (the Schur complement) Gauss's form with three: T1 = Ar Br, T2 = Ai Bi,
 // T3 = (Ar + Ai)(Br + Bi), Re = T1 - T2, Im = T3 - T1 - T2 (the sums formed from
-// the operand fragments in registers), two workgroups per CU.  Its rounding error stays at the FP64 level,
-// bounded by (|Ar| + |Ai|)(|Br| + |Bi|) sums instead of |A||B| ones.
+// the operand fragments in registers), two workgroups per CU.  Its rounding error
+// stays at the FP64 level, bounded by (|Ar| + |Ai|)(|Br| + |Bi|) sums instead of
+// |A||B| ones.
+//
+// The deep product is bound by the FP64 matrix cores, 78.6 TFLOP/s, of which a large
+// real product reaches 72 here.  8192 x 8192 x 16384 takes 95.9 ms, 68.8 TFLOP/s
+// executed (4096 x 4096 x 8192: 12.0 ms, 2048 x 2048 x 4096: 1.54 ms); it took
+// 109.5, 13.4 and 1.69 ms while the compiler chose the order of LDS reads, sums and
+// MFMAs and every global load carried a bounds test.
 //
 // MFMA operand order: the B fragment is fed as the MFMA's first operand and the A
 // fragment as its second, so that the 16 x 16 result lands transposed in the
@@ -64,21 +71,32 @@ __device__ __forceinline__ void zgemm_tile(int tile, int m, int n, int k, cplx a
   const int a_r = tid & 63, a_k = tid >> 6;
   const int b_c = tid >> 2, b_k = (tid & 3) * GM_LPT;
 
-  cplx ra[GM_LPT], rb[GM_LPT];
-  auto gload = [&](int k0) {
+  // Rows past m and columns past n read the last one (their products are not stored),
+  // so the loads of a whole stage carry no test; only the last stage of a depth that is
+  // no multiple of GM_BK does, where both operands become zero past k.
+  st_v2 ra[GM_LPT], rb[GM_LPT];
+  const cplx *pa = A + ((row0 + a_r < m) ? row0 + a_r : m - 1) + (long)a_k * lda;
+  const cplx *pb = B + (long)((col0 + b_c < n) ? col0 + b_c : n - 1) * ldb + b_k;
+  auto gload = [&](int k0) __attribute__((always_inline)) {
+    if (k0 + GM_BK <= k) {
 #pragma unroll
-    for (int u = 0; u < GM_LPT; ++u) {
-      const int kk = k0 + a_k + 4 * u, rr = row0 + a_r;
-      ra[u] = (rr < m && kk < k) ? A[rr + (long)kk * lda] : cmk(0, 0);
-      const int kb = k0 + b_k + u, cc = col0 + b_c;
-      rb[u] = (kb < k && cc < n) ? B[kb + (long)cc * ldb] : cmk(0, 0);
+      for (int u = 0; u < GM_LPT; ++u) {
+        ra[u] = st_ld(pa, (long)(k0 + 4 * u) * lda);
+        rb[u] = st_ld(pb, k0 + u);
+      }
+    } else {
+#pragma unroll
+      for (int u = 0; u < GM_LPT; ++u) {
+        ra[u] = (k0 + a_k + 4 * u < k) ? st_ld(pa, (long)(k0 + 4 * u) * lda) : st_v2{0.0, 0.0};
+        rb[u] = (k0 + b_k + u < k) ? st_ld(pb, k0 + u) : st_v2{0.0, 0.0};
+      }
     }
   };
-  auto sstore = [&](int buf) {
+  auto sstore = [&](int buf) __attribute__((always_inline)) {
 #pragma unroll
     for (int u = 0; u < GM_LPT; ++u) {
-      As[buf][a_k + 4 * u][a_r] = ra[u];
-      Bs[buf][b_k + u][b_c] = rb[u];
+      st_st(&As[buf][a_k + 4 * u][a_r], 0, ra[u]);
+      st_st(&Bs[buf][b_k + u][b_c], 0, rb[u]);
     }
   };
 
@@ -100,21 +118,20 @@ __device__ __forceinline__ void zgemm_tile(int tile, int m, int n, int k, cplx a
   }
   __syncthreads();
   const int fq = lane >> 4, fi = lane & 15;
-  // operand fragments of one k-quad, double buffered in registers so that the LDS
-  // reads of the next quad are in flight during the MFMAs of this one
-  cplx av[2][2], bv[2][2];
-  double as[2][2], bs[2][2];
-  auto fload = [&](int buf, int k4, int slot) {
+  // operand fragments of one k-quad, double buffered in registers: the LDS reads of the
+  // next quad go out ahead of the MFMAs of this one.  The sums of the three-multiplication
+  // form are taken from the fragments between the MFMAs that do not need them and the ones
+  // that do, when the fragments have long arrived.  The scheduler is held to that order:
+  // left alone it put the reads behind the MFMAs and waited for them at the sums.  For
+  // 8192 x 8192 x 16384, eight MFMAs before the sums: 95.9 ms; six: 99.7; the sums spread
+  // over single MFMAs: 99.8; eight, the next stage's LDS stores after the last quad
+  // instead of beside it: 104.6; a raised wave priority over the MFMAs: 105.4.
+  st_v2 av[2][2], bv[2][2];
+  auto fload = [&](int buf, int k4, int slot) __attribute__((always_inline)) {
 #pragma unroll
-    for (int a = 0; a < 2; ++a) av[slot][a] = As[buf][k4 + fq][wm * 32 + a * 16 + fi];
+    for (int a = 0; a < 2; ++a) av[slot][a] = st_ld(&As[buf][k4 + fq][wm * 32 + a * 16 + fi], 0);
 #pragma unroll
-    for (int b = 0; b < 2; ++b) bv[slot][b] = Bs[buf][k4 + fq][wn * 32 + b * 16 + fi];
-    if constexpr (M3) {  // the sums of the three-multiplication form, from the fragments
-#pragma unroll
-      for (int a = 0; a < 2; ++a) as[slot][a] = av[slot][a].x + av[slot][a].y;
-#pragma unroll
-      for (int b = 0; b < 2; ++b) bs[slot][b] = bv[slot][b].x + bv[slot][b].y;
-    }
+    for (int b = 0; b < 2; ++b) bv[slot][b] = st_ld(&Bs[buf][k4 + fq][wn * 32 + b * 16 + fi], 0);
   };
   for (int it = 0; it < nk; ++it) {
     const int buf = it & 1;
@@ -123,36 +140,51 @@ __device__ __forceinline__ void zgemm_tile(int tile, int m, int n, int k, cplx a
 #pragma unroll
     for (int k4 = 0; k4 < GM_BK; k4 += 4) {
       const int cur = (k4 >> 2) & 1;
+      if constexpr (M3) __builtin_amdgcn_sched_barrier(0);
       if (k4 + 4 < GM_BK) fload(buf, k4 + 4, cur ^ 1);
-if constexpr (M3) {
+      // the next stage's values to LDS beside the last quad's MFMAs
+      if (M3 && k4 + 4 == GM_BK && it + 1 < nk) sstore(buf ^ 1);
+      if constexpr (M3) {
 #pragma unroll
-      for (int a = 0; a < 2; ++a)
+        for (int a = 0; a < 2; ++a)
 #pragma unroll
-        for (int b = 0; b < 2; ++b) {
-          accr[a][b] = mfma16(bv[cur][b].x, av[cur][a].x, accr[a][b]);
-          acci[a][b] = mfma16(bv[cur][b].y, av[cur][a].y, acci[a][b]);
-          accs[a][b] = mfma16(bs[cur][b], as[cur][a], accs[a][b]);
-        }
-} else {
+          for (int b = 0; b < 2; ++b) {
+            accr[a][b] = mfma16(bv[cur][b].x, av[cur][a].x, accr[a][b]);
+            acci[a][b] = mfma16(bv[cur][b].y, av[cur][a].y, acci[a][b]);
+          }
+        double as[2], bs[2];
 #pragma unroll
-      for (int a = 0; a < 2; ++a)
+        for (int a = 0; a < 2; ++a) as[a] = av[cur][a].x + av[cur][a].y;
 #pragma unroll
-        for (int b = 0; b < 2; ++b) accr[a][b] = mfma16(bv[cur][b].x, av[cur][a].x, accr[a][b]);
+        for (int b = 0; b < 2; ++b) bs[b] = bv[cur][b].x + bv[cur][b].y;
 #pragma unroll
-      for (int a = 0; a < 2; ++a)
+        for (int a = 0; a < 2; ++a)
 #pragma unroll
-        for (int b = 0; b < 2; ++b) acci[a][b] = mfma16(bv[cur][b].y, av[cur][a].x, acci[a][b]);
+          for (int b = 0; b < 2; ++b) accs[a][b] = mfma16(bs[b], as[a], accs[a][b]);
+        if (k4 + 4 < GM_BK) __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);  // LDS reads
+        __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);                      // MFMA
+        __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);                      // the sums
+        __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
+      } else {
 #pragma unroll
-      for (int a = 0; a < 2; ++a)
+        for (int a = 0; a < 2; ++a)
 #pragma unroll
-        for (int b = 0; b < 2; ++b) accr[a][b] = mfma16(bv[cur][b].y, -av[cur][a].y, accr[a][b]);
+          for (int b = 0; b < 2; ++b) accr[a][b] = mfma16(bv[cur][b].x, av[cur][a].x, accr[a][b]);
 #pragma unroll
-      for (int a = 0; a < 2; ++a)
+        for (int a = 0; a < 2; ++a)
 #pragma unroll
-        for (int b = 0; b < 2; ++b) acci[a][b] = mfma16(bv[cur][b].x, av[cur][a].y, acci[a][b]);
-}
+          for (int b = 0; b < 2; ++b) acci[a][b] = mfma16(bv[cur][b].y, av[cur][a].x, acci[a][b]);
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+          for (int b = 0; b < 2; ++b) accr[a][b] = mfma16(bv[cur][b].y, -av[cur][a].y, accr[a][b]);
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+          for (int b = 0; b < 2; ++b) acci[a][b] = mfma16(bv[cur][b].x, av[cur][a].y, acci[a][b]);
+      }
     }
-    if (it + 1 < nk) sstore(buf ^ 1);
+    if (!M3 && it + 1 < nk) sstore(buf ^ 1);
     __syncthreads();
   }
 
