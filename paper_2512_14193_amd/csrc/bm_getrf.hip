@@ -923,7 +923,8 @@ static int lu_gemm(hipStream_t st, int m, int n, int k, const cplx *A, long lda,
 static int lu_gemm(hipStream_t st, int m, int n, int k, const cplx32 *A, long lda, const cplx32 *B, long ldb,
                    cplx32 *C, long ldc, bool next, int) {
   const cplx one = cmk(1.0, 0.0), mone = cmk(-1.0, 0.0);
-  return (next ? bm_launch_zgemm_shallow_c64 : bm_launch_zgemm32_cc)(st, m, n, k, mone, A, lda, B, ldb, one, C, ldc);
+  if (!next) return bm_launch_update32(st, m, n, k, A, lda, B, ldb, C, ldc);
+  return bm_launch_zgemm_shallow_c64(st, m, n, k, mone, A, lda, B, ldb, one, C, ldc);
 }
 
 // The interchanges of the panel at column j (jb columns, list swp) on the columns
@@ -1057,7 +1058,7 @@ static int lu_gemm_batch(const cplx *, hipStream_t st, int count, const bm_lu_ba
 }
 static int lu_gemm_batch(const cplx32 *, hipStream_t st, int count, const bm_lu_batch &bb, int m, int n, int k,
                          long oa, long lda, long ob, long oc, bool next) {
-  return (next ? bm_launch_zgemm_shallow_lu_batch_c64 : bm_launch_zgemm32_lu_batch)(st, count, bb, m, n, k, oa, lda, ob,
+  return (next ? bm_launch_zgemm_shallow_lu_batch_c64 : bm_launch_update32_batch)(st, count, bb, m, n, k, oa, lda, ob,
                                                                                     lda, oc, lda);
 }
 

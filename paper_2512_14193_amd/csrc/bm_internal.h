@@ -125,6 +125,21 @@ __device__ inline void st_z(cplx32 *A, long i, st_v2 v) {
   *reinterpret_cast<st_f2 *>(A + i) = st_f2{(float)v.x, (float)v.y};
 }
 __device__ inline st_v2 to_v2(cplx v) { return st_v2{v.x, v.y}; }
+// Output tile of workgroup b in a grid of tm x tn tiles.  Workgroups are dealt to
+// the eight XCDs in turn (XCD b % 8); XCD x takes the x-th consecutive range of a
+// tile order that walks groups of eight tile rows column by column, so that the
+// workgroups one XCD runs together (64 at two per CU) form about an 8 x 8 block of
+// C and share its eight A row panels and eight B column panels in that XCD's L2.
+// A bijection of [0, tm tn) for any tile count (the first T % 8 XCDs take one
+// tile more); the tiles' arithmetic does not depend on it.
+__device__ inline int bm_tile_of(int b, int tm, int tn) {
+  const int T = tm * tn, q = T / 8, r = T % 8, x = b % 8;
+  const int t = x * q + (x < r ? x : r) + b / 8;
+  const int gsz = 8 * tn, grp = t / gsz, gi = t % gsz;
+  const int grows = (tm - grp * 8 < 8) ? tm - grp * 8 : 8;
+  return grp * 8 + gi % grows + (gi / grows) * tm;
+}
+
 // Product of a 64 x 64 complex tile with a group of eight complex columns on the
 // FP64 matrix cores (v_mfma_f64_16x16x4f64), both operands in registers, for a
 // workgroup whose wavefront w owns rows 16 w .. 16 w + 15.  Lane (fi, fq) =
@@ -256,8 +271,8 @@ int bm_launch_zgemm32(hipStream_t s, int m, int n, int k, cplx alpha, const cplx
 // arithmetic on the widened values)
 int bm_launch_zgemm32_c(hipStream_t s, int m, int n, int k, cplx alpha, const cplx *A, int64_t lda, const cplx *B,
                         int64_t ldb, cplx beta, cplx32 *C, int64_t ldc);
-int bm_launch_zgemm32_cc(hipStream_t s, int m, int n, int k, cplx alpha, const cplx32 *A, int64_t lda,
-                         const cplx32 *B, int64_t ldb, cplx beta, cplx32 *C, int64_t ldc);
+int bm_launch_update32(hipStream_t s, int m, int n, int k, const cplx32 *A, int64_t lda, const cplx32 *B, int64_t ldb,
+                       cplx32 *C, int64_t ldc);
 // Per-problem pointers of a batched LU launch (blockIdx.y selects the problem):
 // same order, same leading dimension, one workspace each
 struct bm_lu_batch {  // (BM_LU_BATCH_MAX: include/bm.h)
@@ -273,8 +288,8 @@ int bm_launch_zgemm_lu_batch(hipStream_t s, int count, const bm_lu_batch &bb, in
 // shallow kernel for the next panel's update, the FP32 matrix cores for the rest
 int bm_launch_zgemm_shallow_lu_batch_c64(hipStream_t s, int count, const bm_lu_batch &bb, int m, int n, int k, long oa,
                                         long lda, long ob, long ldb, long oc, long ldc);
-int bm_launch_zgemm32_lu_batch(hipStream_t s, int count, const bm_lu_batch &bb, int m, int n, int k, long oa,
-                               long lda, long ob, long ldb, long oc, long ldc);
+int bm_launch_update32_batch(hipStream_t s, int count, const bm_lu_batch &bb, int m, int n, int k, long oa, long lda,
+                             long ob, long ldb, long oc, long ldc);
 // The split-FP16 product into complex64 C (bm_zgemm16.hip): workspace bytes for
 // k chunks of kc, and the launcher (chunks_out: the number of k-chunks taken)
 // (the mixed-precision Schur complement takes it from this N on)

@@ -7,9 +7,9 @@
 //
 // Used in the mixed-precision factorisation: the Schur complement
 // U33 = -[M31 M32][M13; M23] of Theorem (thm:LU) from the FP64 blocks into a
-// complex64 U33, and the trailing updates of its FP32 LU (all three operands
-// complex64); FP64 iterative refinement against the FP64 blocks then recovers the
-// FP64 solution.
+// complex64 U33; the trailing updates of its FP32 LU (all three operands complex64)
+// have a kernel of their own below.  FP64 iterative refinement against the FP64
+// blocks then recovers the FP64 solution.
 //
 // Tiling: a workgroup of 256 threads (4 wave64s, 2 x 2) owns a 128 x 128 tile of
 // C, two workgroups per CU (accumulators in VGPRs, no spills); each wave owns
@@ -185,23 +185,145 @@ __global__ __launch_bounds__(256, G2_OCC) void zgemm32_kernel(int m, int n, int 
   zgemm32_tile<BETA0, TA, TB, TC>(blockIdx.x, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, tiles_m);
 }
 
-// The complex64 LU's trailing update C -= A B for a batch of problems (blockIdx.y),
-// each operand at an element offset into that problem's complex64 matrix
-__global__ __launch_bounds__(256, G2_OCC) void zgemm32_update_batch_kernel(bm_lu_batch bb, int m, int n, int k,
-                                                                        long oa, long lda, long ob, long ldb,
-                                                                        long oc, long ldc, int tiles_m) {
-  cplx32 *M = (cplx32 *)bb.A[blockIdx.y];
-  zgemm32_tile<false, cplx32, cplx32, cplx32>(blockIdx.x, m, n, k, cmk(-1.0, 0.0), M + oa, lda, M + ob, ldb,
-                                              cmk(1.0, 0.0), M + oc, ldc, tiles_m);
+// ---------------------------------------------------------------------------
+// The trailing update of the complex64 LU, C -= A B with k = 64: a workgroup of 256
+// threads (2 x 2 waves) owns a 64 x 64 tile of C, each wave one 32 x 32 block, four
+// workgroups per CU.
+//
+// Large updates are bound by the traffic of C (read and written once: 3.3 TB/s, with
+// the matrix cores at 79 TFLOP/s of 157), small ones by one tile's chain of loads and
+// products.  A 64 x 64 tile has a quarter of that chain of the 128 x 128 tile of the
+// product above, and C comes in beside the last products instead of after them.
+// Times of an R x R update, with the 128 x 128 tile -> with this one:
+// R = 8064 480 -> 317 us, 4096 116 -> 84, 2048 42 -> 25, 1024 37 -> 9.9, 200 32 -> 8.3.
+// The products and their order are the same, and so are the results bit for bit.
+// ---------------------------------------------------------------------------
+#define U3_T 64
+#define U3_BK 16
+#define U3_PAD 2  // complex values: B is written 16 k by 4 columns, the banks of which then differ
+#define U3_LPT (U3_BK * U3_T / 256)
+
+__device__ __forceinline__ void update32_tile(int tile, int m, int n, int k, const cplx32 *__restrict__ A, long lda,
+                                              const cplx32 *__restrict__ B, long ldb, cplx32 *__restrict__ C, long ldc,
+                                              int tiles_m) {
+  __shared__ st_f2 As[2][U3_BK][U3_T];
+  __shared__ st_f2 Bs[2][U3_BK][U3_T + U3_PAD];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wm = wave & 1, wn = wave >> 1;
+  const int row0 = (tile % tiles_m) * U3_T, col0 = (tile / tiles_m) * U3_T;
+
+  // A: row tid % 64, k = tid / 64 + 4 u;  B: k = tid % 16, column tid / 16 + 16 u.  Rows
+  // past m and columns past n read the last one (their products are not stored).
+  const int a_r = tid & 63, a_k = tid >> 6, b_k = tid & 15, b_c = tid >> 4;
+  const cplx32 *pa = A + ((row0 + a_r < m) ? row0 + a_r : m - 1) + (long)a_k * lda;
+  const cplx32 *pb[U3_LPT];
+#pragma unroll
+  for (int u = 0; u < U3_LPT; ++u) {
+    const int cc = col0 + b_c + 16 * u;
+    pb[u] = B + (long)((cc < n) ? cc : n - 1) * ldb + b_k;
+  }
+  auto ld = [](const cplx32 *p) __attribute__((always_inline)) { return *reinterpret_cast<const st_f2 *>(p); };
+  st_f2 ra[U3_LPT], rb[U3_LPT];
+  auto gload = [&](int k0) __attribute__((always_inline)) {
+    if (k0 + U3_BK <= k) {
+#pragma unroll
+      for (int u = 0; u < U3_LPT; ++u) {
+        ra[u] = ld(pa + (long)(k0 + 4 * u) * lda);
+        rb[u] = ld(pb[u] + k0);
+      }
+    } else {
+#pragma unroll
+      for (int u = 0; u < U3_LPT; ++u) {
+        ra[u] = (k0 + a_k + 4 * u < k) ? ld(pa + (long)(k0 + 4 * u) * lda) : st_f2{0.f, 0.f};
+        rb[u] = (k0 + b_k < k) ? ld(pb[u] + k0) : st_f2{0.f, 0.f};
+      }
+    }
+  };
+  auto sstore = [&](int buf) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < U3_LPT; ++u) {
+      As[buf][a_k + 4 * u][a_r] = ra[u];
+      Bs[buf][b_k][b_c + 16 * u] = rb[u];
+    }
+  };
+
+  f32x16 t1, t2, t3;  // sum Ar Br, sum Ai Bi, sum (Ar + Ai)(Br + Bi)
+#pragma unroll
+  for (int r = 0; r < 16; ++r) t1[r] = t2[r] = t3[r] = 0.f;
+  const int fh = lane >> 5, fi = lane & 31;
+  auto stage = [&](int buf) __attribute__((always_inline)) {
+#pragma unroll
+    for (int k2 = 0; k2 < U3_BK; k2 += 2) {
+      __builtin_amdgcn_sched_barrier(0);  // a pair at a time: 3% faster than the compiler's interleaving
+      const st_f2 av = As[buf][k2 + fh][wm * 32 + fi], bv = Bs[buf][k2 + fh][wn * 32 + fi];
+      t1 = mfma32(bv.x, av.x, t1);
+      t2 = mfma32(bv.y, av.y, t2);
+      t3 = mfma32(bv.x + bv.y, av.x + av.y, t3);
+    }
+  };
+  const int nk = (k + U3_BK - 1) / U3_BK;
+  gload(0);
+  sstore(0);
+  __syncthreads();
+  for (int it = 0; it + 1 < nk; ++it) {
+    gload((it + 1) * U3_BK);
+    stage(it & 1);
+    sstore((it + 1) & 1);
+    __syncthreads();
+  }
+  // C comes in beside the last stage.  Lane l, register r: row l % 32, column
+  // (r % 4) + 8 (r / 4) + 4 (l / 32) of the wave's block.
+  const int row = row0 + wm * 32 + fi, colb = col0 + wn * 32 + 4 * fh;
+  const int rowc = (row < m) ? row : m - 1;
+  st_f2 cin[16];
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int col = colb + (r & 3) + 8 * (r >> 2);
+    cin[r] = ld(C + rowc + (long)((col < n) ? col : n - 1) * ldc);
+  }
+  stage((nk - 1) & 1);
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int col = colb + (r & 3) + 8 * (r >> 2);
+    const float re = t1[r] - t2[r], im = t3[r] - t1[r] - t2[r];
+    if (row < m && col < n)
+      *reinterpret_cast<st_f2 *>(C + row + (long)col * ldc) = st_f2{cin[r].x - re, cin[r].y - im};
+  }
 }
 
-int bm_launch_zgemm32_lu_batch(hipStream_t s, int count, const bm_lu_batch &bb, int m, int n, int k, long oa,
-                               long lda, long ob, long ldb, long oc, long ldc) {
-  if (m <= 0 || n <= 0) return BM_OK;
+__global__ __launch_bounds__(256, 4) void update32_kernel(int m, int n, int k, const cplx32 *__restrict__ A, long lda,
+                                                          const cplx32 *__restrict__ B, long ldb,
+                                                          cplx32 *__restrict__ C, long ldc, int tiles_m) {
+  update32_tile(bm_tile_of(blockIdx.x, tiles_m, (n + U3_T - 1) / U3_T), m, n, k, A, lda, B, ldb, C, ldc, tiles_m);
+}
+
+// The same for a batch of problems (blockIdx.y), each operand at an element offset
+// into that problem's matrix
+__global__ __launch_bounds__(256, 4) void update32_batch_kernel(bm_lu_batch bb, int m, int n, int k, long oa, long lda,
+                                                                long ob, long ldb, long oc, long ldc, int tiles_m) {
+  cplx32 *M = (cplx32 *)bb.A[blockIdx.y];
+  update32_tile(blockIdx.x, m, n, k, M + oa, lda, M + ob, ldb, M + oc, ldc, tiles_m);
+}
+
+int bm_launch_update32(hipStream_t s, int m, int n, int k, const cplx32 *A, int64_t lda, const cplx32 *B, int64_t ldb,
+                       cplx32 *C, int64_t ldc) {
+  if (m <= 0 || n <= 0 || k <= 0) return BM_OK;
+  const int tm = (m + U3_T - 1) / U3_T, tn = (n + U3_T - 1) / U3_T;
+  const long tiles = (long)tm * tn;
+  if (tiles > 0x7fffffffL) return BM_E_ARG;
+  hipLaunchKernelGGL(update32_kernel, dim3((unsigned)tiles), dim3(256), 0, s, m, n, k, A, (long)lda, B, (long)ldb, C,
+                     (long)ldc, tm);
+  BM_HIP_TRY(hipGetLastError());
+  return BM_OK;
+}
+
+int bm_launch_update32_batch(hipStream_t s, int count, const bm_lu_batch &bb, int m, int n, int k, long oa, long lda,
+                             long ob, long ldb, long oc, long ldc) {
+  if (m <= 0 || n <= 0 || k <= 0) return BM_OK;
   if (count < 1 || count > BM_LU_BATCH_MAX) return BM_E_ARG;
-  const int tm = (m + G2_BM - 1) / G2_BM, tn = (n + G2_BN - 1) / G2_BN;
-  hipLaunchKernelGGL(zgemm32_update_batch_kernel, dim3((unsigned)(tm * tn), count), dim3(256), 0, s, bb, m, n, k, oa,
-                     lda, ob, ldb, oc, ldc, tm);
+  const int tm = (m + U3_T - 1) / U3_T, tn = (n + U3_T - 1) / U3_T;
+  hipLaunchKernelGGL(update32_batch_kernel, dim3((unsigned)(tm * tn), count), dim3(256), 0, s, bb, m, n, k, oa, lda, ob,
+                     ldb, oc, ldc, tm);
   BM_HIP_TRY(hipGetLastError());
   return BM_OK;
 }
@@ -230,10 +352,5 @@ int bm_launch_zgemm32(hipStream_t s, int m, int n, int k, cplx alpha, const cplx
 
 int bm_launch_zgemm32_c(hipStream_t s, int m, int n, int k, cplx alpha, const cplx *A, int64_t lda, const cplx *B,
                         int64_t ldb, cplx beta, cplx32 *C, int64_t ldc) {
-  return launch32(s, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc);
-}
-
-int bm_launch_zgemm32_cc(hipStream_t s, int m, int n, int k, cplx alpha, const cplx32 *A, int64_t lda,
-                         const cplx32 *B, int64_t ldb, cplx beta, cplx32 *C, int64_t ldc) {
   return launch32(s, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc);
 }
