@@ -3,7 +3,7 @@
 // Used for U33 = -M31 M13 - M32 M23 (Theorem thm:LU) and, as the comparator, for
 // the 2N x 2N ordinary matrix.  Per panel of jb <= 64 columns starting at column j:
 //
-//  1. the panel factorisation.  Up to 2048 rows: panel_stream_kernel
+//  1. the panel factorisation.  Up to 2688 rows: panel_stream_kernel
 //     (bm_panel_stream.h), each workgroup holding a few columns over all rows.
 //     Beyond: panel_kernel (P workgroups, all resident at once): the (n - j) x jb
 //     panel is held in LDS for the whole panel, 128 consecutive rows per
@@ -796,13 +796,13 @@ using panel_fn = void (*)(int, T *, long, int, int, int, int32_t *, int32_t *, c
                           bm_lu_batch);
 // By kind of panel (lu_shape): the streaming panels by rows per thread and columns
 // per workgroup, then the exchanging panel.
-#define PANEL_KINDS 5
+#define PANEL_KINDS 6
 template <class T, bool BAT>
 static panel_fn<T> panel_fn_of(int kind) {
   static const panel_fn<T> fns[PANEL_KINDS] = {
       panel_stream_kernel<64, 1, 8, T, BAT>,  panel_stream_kernel<256, 2, 4, T, BAT>,
       panel_stream_kernel<512, 2, 4, T, BAT>, panel_stream_kernel<512, 4, 4, T, BAT>,
-      panel_kernel<T, BAT>};
+      panel_stream_kernel<448, 6, 4, T, BAT>, panel_kernel<T, BAT>};
   return fns[kind];
 }
 
@@ -834,22 +834,26 @@ int bm_fill_u64(hipStream_t s, void *p, size_t n, unsigned long long v) {
 //    512       60 (256x2x4), 65 (512x1x4)           130
 //   1024       72 (512x2x4), 77 (x8), 76 (256x4x4)  130
 //   2048       94 (512x4x4), 108 (x2), 125 (1024x2x4)  131 to 155
-//   4096      167 (512x8x4), 386 (512x8x2, spilled) 152
-// so beyond 2048 rows, where a thread's rows no longer leave registers for the
-// clerk's wavefront, the exchanging panel (128 rows per workgroup) takes over.
+//   2688      119 (448x6x4)                         150
+//   3136      306 (448x8x4, spilled)                151
+//   4032      167 (512x8x4), 200 (448x9x2)          152
+// A thread of 512 or fewer holds 256 registers, which six rows of four columns fill with
+// the next column's multipliers on their way.  Beyond 2688 rows they cannot be on their
+// way, or a workgroup holds two columns, and reading the earlier columns becomes the
+// chain: the exchanging panel (128 rows per workgroup) takes over.
 struct lu_shape {
   int kind, wgs, threads, fill_h;
   long fill_n;
   size_t lds;
 };
-#define PANEL_STREAM_MAX_R 2048
+#define PANEL_STREAM_MAX_R 2688
 static bool panel_shape(int R, int jb, int ncu, lu_shape *o) {
   // (the exchanging panel's workgroup count bounds the orders taken, whichever runs)
   const int pmax = (ncu < PANEL_PMAX) ? ncu : PANEL_PMAX;
   const int P = (R + 127) / 128;
   if (P < 1 || ((R > 2048) ? P : (R + 63) / 64) > pmax) return false;
   if (R <= PANEL_STREAM_MAX_R) {
-    static const int cw[PANEL_KINDS - 1] = {8, 4, 4, 4}, nt[PANEL_KINDS - 1] = {64, 256, 512, 512};
+    static const int cw[PANEL_KINDS - 1] = {8, 4, 4, 4, 4}, nt[PANEL_KINDS - 1] = {64, 256, 512, 512, 448};
     int k = (R <= LU_NB) ? 0 : 1;
     while (k > 0 && R > (256 << k)) ++k;
     o->kind = k;

@@ -20,8 +20,8 @@
 // few cycles, so the search compares the high words of |Re| + |Im| only (an integer
 // maximum).  Where two rows share the largest high word, or the largest is zero,
 // denormal, infinite or NaN, the column takes the exact search instead.  Measured per
-// column: 0.65 us at 64 rows to 1.25 us at 2048 (2.05 us with an exchange of candidates
-// between 32 workgroups of 64 rows), a hand-off between workgroups 0.5 to 1 us.
+// column: 0.65 us at 64 rows to 1.25 us at 2048 and 1.7 at 2688 (2.05 to 2.3 us with an exchange of
+// candidates between workgroups of 64 or 128 rows), a hand-off between workgroups 0.5 to 1 us.
 //
 // Exchange words, each 16 bytes, written once with agent scope over the empty
 // pattern and polled by the readers:
@@ -101,6 +101,7 @@ __global__ __launch_bounds__(NT + 64) void panel_stream_kernel(int N, T *A, long
     swp = bb.swp[b];
   }
   constexpr int NW = NT / 64;  // wavefronts that hold rows; wavefront NW is the clerk
+  constexpr int NWP = (NW > 8) ? 16 : (NW > 4) ? 8 : NW;  // lanes that compare their candidates
   static_assert(CW <= 16 && (CW & (CW - 1)) == 0 && NW <= 16, "a pivot row lies in a row of 16 lanes");
   // only the last panel of a matrix (at most 64 rows) can have fewer than 64 columns
   constexpr bool FULL = NT * RPT > LU_NB;
@@ -115,6 +116,7 @@ __global__ __launch_bounds__(NT + 64) void panel_stream_kernel(int N, T *A, long
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave_of_lane = min(lane & (NWP - 1), NW - 1);
   const int g = (int)blockIdx.x, c0 = g * CW, R = N - j;
   const int nst = (FULL || c0 < jb) ? c0 : jb;  // columns of the earlier workgroups
   const __amdgpu_buffer_rsrc_t rs = rec_rsrc(slots);
@@ -143,8 +145,8 @@ __global__ __launch_bounds__(NT + 64) void panel_stream_kernel(int N, T *A, long
     bool fast;
   };
   auto winner = [&](int sb) __attribute__((always_inline)) {
-    const int4 h = s_h[sb][lane & (NW - 1)];
-    const int hm = __builtin_amdgcn_readfirstlane(group_max_i32<NW>(h.x));
+    const int4 h = s_h[sb][wave_of_lane];
+    const int hm = __builtin_amdgcn_readfirstlane(group_max_i32<NWP>(h.x));
     const unsigned mk = (unsigned)(__ballot(h.x == hm) & ((1ull << NW) - 1));
     pick o;
     o.ww = __ffs((int)mk) - 1;
@@ -199,7 +201,7 @@ __global__ __launch_bounds__(NT + 64) void panel_stream_kernel(int N, T *A, long
         track_end();
         if (lane == 0) s_pick = 0x7fffffff;
         spn_barrier();
-        zero = (wave_max_f64(s_hv[lane & (NW - 1)]) > 0.0) ? 0 : 1;
+        zero = (wave_max_f64(s_hv[wave_of_lane]) > 0.0) ? 0 : 1;
         spn_barrier();
         o.slot = __builtin_amdgcn_readfirstlane(min(s_pick & 0xffff, NT * RPT - 1));
         o.ww = 0;
@@ -279,8 +281,8 @@ __global__ __launch_bounds__(NT + 64) void panel_stream_kernel(int N, T *A, long
   }
   spn_barrier();
   // a pivot row leaves the search (with_row(k) in the thread that holds it)
-  auto retire = [&](int slot, auto &&with_row) __attribute__((always_inline)) {
-    if ((slot & (NT - 1)) >> 6 == wave) {
+  auto retire = [&](unsigned slot, auto &&with_row) __attribute__((always_inline)) {
+    if (slot % NT >> 6 == wave) {
 #pragma unroll
       for (int k = 0; k < RPT; ++k)
         if (slot / NT == k && lane == (slot & 63)) {
@@ -407,7 +409,7 @@ __global__ __launch_bounds__(NT + 64) void panel_stream_kernel(int N, T *A, long
         v = wave_max_f64(v);
         if (lane == 0) s_hv[wave] = v;
         spn_barrier();
-        const double vm = wave_max_f64(s_hv[lane & (NW - 1)]);
+        const double vm = wave_max_f64(s_hv[wave_of_lane]);
         int best = 0x7fffffff;
 #pragma unroll
         for (int k = 0; k < RPT; ++k) {
