@@ -1255,12 +1255,12 @@ static double sp_time(int tiles, int ks, int slots, int k, double per_k) {
   return rounds * per_k * kc + (ks > 1 ? 0.006 : 0.0);
 }
 
-// Returns 1 when, with a panel of the chain taking beta ms, the planned product ends before the chain of panels (the overlap
+// per_k1, per_k2: ms per unit of k of a round of tiles, one workgroup per CU and two (block 0,
+// whole device).  Returns 1 when, with a panel of the chain taking beta ms, the planned product ends before the chain of panels (the overlap
 // pays), else 0 (then the product is better formed in full first).
-static int sp_plan_at(double beta, int n, int k, int ncu, int gs, size_t w_cap, sp_seg *seg, int *nseg_out) {
+static int sp_plan_at(double beta, double per_k1, double per_k2, int n, int k, int ncu, int gs, size_t w_cap, sp_seg *seg,
+                      int *nseg_out) {
   const int B = (n + LU_NB - 1) / LU_NB, tb = B;  // blocks; row tiles of a block
-  const double per_k1 = 0.49 / 4096.0;            // ms per unit of k: one workgroup per CU
-  const double per_k2 = 0.84 / 4096.0;            // two per CU (block 0, whole device)
   const double margin = 0.03;
   int nseg = 0;
   const int ks0 = sp_ksplit(tb, 2 * ncu, k, w_cap);
@@ -1304,10 +1304,21 @@ static int sp_plan_at(double beta, int n, int k, int ncu, int gs, size_t w_cap, 
 // the chain in ways the model leaves out, so a plan of many segments loses what it gains
 // (n = 1728: 9 segments 3.41 ms, 14 segments 4.30, 7 segments 3.74, product first 4.23;
 // n = 2048: 9 segments 4.72, 13 segments 5.45, 24 segments 7.35, product first 5.20).
+// First with the product an eighth slower than it runs alone, which leaves it room beside
+// the updates (n = 1728: 3.25 ms, planned at its own rate 3.50), then, where that finds
+// none, at its own rate and with the panels of more than 2048 rows in mind, 0.12 to 0.15 ms
+// and the launches (product first -> beside the panels: n = 2176 5.77 -> 5.18 ms,
+// 2240 6.00 -> 5.81, 2368 6.88 -> 6.41, 2432 7.12 -> 6.78; from 2560 on no plan is found).
 #define SP_FEW 10
 static int sp_plan(int n, int k, int ncu, int gs, size_t w_cap, sp_seg *seg, int *nseg_out) {
   for (int i = 0; i <= 4; ++i)
-    if (sp_plan_at(0.09 + 0.015 * i, n, k, ncu, gs, w_cap, seg, nseg_out) && *nseg_out <= SP_FEW) return 1;
+    if (sp_plan_at(0.09 + 0.015 * i, 0.49 / 4096, 0.84 / 4096, n, k, ncu, gs, w_cap, seg, nseg_out) &&
+        *nseg_out <= SP_FEW)
+      return 1;
+  for (int i = 0; i <= 7; ++i)
+    if (sp_plan_at(0.09 + 0.015 * i, 0.43 / 4096, 0.74 / 4096, n, k, ncu, gs, w_cap, seg, nseg_out) &&
+        *nseg_out <= SP_FEW)
+      return 1;
   return 0;
 }
 
