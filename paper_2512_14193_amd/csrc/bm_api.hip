@@ -123,9 +123,9 @@ int bm_create(int32_t n, int32_t formulation, void *hip_stream, bm_problem **out
   p->prec = BM_PREC_FP64;
   p->ir_tol = 1e-12;
   p->ir_maxit = 10;
-  if (ok) p->gws = bm_getrf_ws_create(p->nf);
+  if (ok) p->gws = bm_getrf_ws_create(p->nf, p->stream);
   // the Schur complement beside the LU (mixed form, FP64, N <= BM_PIPE_MAX_N); its
-  // two extra streams are created by the first factorisation that uses them
+  // two extra streams are made by the first factorisation on this stream that uses them
   if (ok && p->gws && p->pipe_w) p->pipeline = 1;
   if (!ok || !p->gws) {
     free_problem(p);
@@ -773,7 +773,7 @@ int bm_zgetrf(void *hip_stream, int32_t n, void *A, int64_t lda, int32_t *ipiv, 
     return BM_OK;
   }
   hipStream_t s = (hipStream_t)hip_stream;
-  bm_getrf_ws *w = bm_getrf_ws_create(n);
+  bm_getrf_ws *w = bm_getrf_ws_create(n, s);
   int32_t *dev_err = nullptr;
   if (!w || hipMalloc(&dev_err, 2 * sizeof(int32_t)) != hipSuccess) {
     bm_getrf_ws_destroy(w);

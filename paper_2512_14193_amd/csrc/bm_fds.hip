@@ -378,7 +378,7 @@ int invert(bm_fds *f, const std::vector<inv_job> &jobs) {
     if (int rc2 = refine_inverses(f, jobs)) return rc2;
   }
   if (nmax_big > 0) {
-    bm_getrf_ws *w = bm_getrf_ws_create(nmax_big);
+    bm_getrf_ws *w = bm_getrf_ws_create(nmax_big, s);
     int32_t *ipiv = nullptr, *perm = nullptr;
     cplx *dinv = nullptr, *T = nullptr;
     const int nblk = (nmax_big + 63) / 64;
@@ -1057,7 +1057,7 @@ int factor_all(bm_fds *f) {
       f->root_ws = nullptr;
     }
     if (!f->root_ws) {
-      f->root_ws = bm_getrf_ws_create(m);
+      f->root_ws = bm_getrf_ws_create(m, f->stream);
       if (!f->root_ws) return BM_E_NOMEM;
       f->root_ws_n = m;
     }

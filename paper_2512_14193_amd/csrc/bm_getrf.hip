@@ -751,7 +751,74 @@ __global__ __launch_bounds__(256) void swap_trsm_kernel(T *A, long lda, int j, i
 struct bm_lu_pipe;
 static void pipe_destroy(bm_lu_pipe *q);
 
-bm_getrf_ws *bm_getrf_ws_create(int n) {
+// The streams beside a problem's own: one set for all workspaces of a stream and device,
+// made with the first of them and destroyed with the last.  Streams share four hardware
+// queues, in which a wait of one stream holds up the others.  With a set per workspace the
+// three streams of an overlapped factorisation met their problem's own in a queue as soon
+// as a second problem was alive (n = 2048, three problems: 6.25, 6.46 and 4.40 ms).  What
+// problems on one stream do follows each other anyway, so they lose nothing by sharing;
+// every wait is for work enqueued before it, so a shared stream cannot close a circle.
+// Workspaces of the per-thread default stream, one handle for many streams, share none.
+struct bm_lu_side {
+  int dev = 0, refs = 1;
+  hipStream_t key = nullptr, aux = nullptr, g = nullptr, c = nullptr;
+  bm_lu_side *next = nullptr;
+};
+static std::mutex side_mutex;
+static bm_lu_side *side_list = nullptr;
+
+static bm_lu_side *side_acquire(hipStream_t s) {
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return nullptr;
+  std::lock_guard<std::mutex> lk(side_mutex);
+  if (s != hipStreamPerThread)
+    for (bm_lu_side *d = side_list; d; d = d->next)
+      if (d->dev == dev && d->key == s) {
+        ++d->refs;
+        return d;
+      }
+  bm_lu_side *d = new (std::nothrow) bm_lu_side();
+  if (!d) return nullptr;
+  d->dev = dev;
+  d->key = s;
+  if (hipStreamCreateWithFlags(&d->aux, hipStreamNonBlocking) != hipSuccess) {
+    delete d;
+    return nullptr;
+  }
+  d->next = side_list;
+  side_list = d;
+  return d;
+}
+
+// the two streams of the overlapped product, made on its first use
+static bool side_pipe_streams(bm_lu_side *d) {
+  std::lock_guard<std::mutex> lk(side_mutex);
+  for (hipStream_t *q : {&d->g, &d->c})
+    if (!*q && hipStreamCreateWithFlags(q, hipStreamNonBlocking) != hipSuccess) {
+      *q = nullptr;
+      return false;
+    }
+  return true;
+}
+
+static void side_release(bm_lu_side *d) {
+  if (!d) return;
+  {
+    std::lock_guard<std::mutex> lk(side_mutex);
+    if (--d->refs > 0) return;
+    bm_lu_side **at = &side_list;
+    while (*at != d) at = &(*at)->next;
+    *at = d->next;
+  }
+  for (hipStream_t q : {d->aux, d->g, d->c})
+    if (q) {
+      (void)hipStreamSynchronize(q);
+      (void)hipStreamDestroy(q);
+    }
+  delete d;
+}
+
+bm_getrf_ws *bm_getrf_ws_create(int n, hipStream_t s) {
   bm_getrf_ws *w = new bm_getrf_ws();
   w->n = n;
   w->npanel = (n + LU_NB - 1) / LU_NB;
@@ -759,7 +826,8 @@ bm_getrf_ws *bm_getrf_ws_create(int n) {
   bool ok = hipMalloc(&w->slots, sizeof(cplx) * 2 * SLOT_ELEMS) == hipSuccess;
   ok = ok && hipMalloc(&w->swp, sizeof(int32_t) * (size_t)w->npanel * SWP_STRIDE) == hipSuccess;
   ok = ok && hipMalloc(&w->zbuf, sizeof(cplx) * (1 + 2 * (size_t)nblk * BM_DIAG_NB * BM_MAX_NRHS)) == hipSuccess;
-  ok = ok && hipStreamCreateWithFlags(&w->aux, hipStreamNonBlocking) == hipSuccess;
+  ok = ok && (w->side = side_acquire(s)) != nullptr;
+  if (ok) w->aux = w->side->aux;
   // the lookahead events only order the two streams of this device: no system-scope
   // fence (the host never inspects them)
   ok = ok && hipEventCreateWithFlags(&w->e_next, hipEventDisableTiming | BM_LU_EVENT_FLAGS) == hipSuccess;
@@ -776,13 +844,10 @@ void bm_getrf_ws_destroy(bm_getrf_ws *w) {
   (void)hipFree(w->slots);
   (void)hipFree(w->swp);
   (void)hipFree(w->zbuf);
-  if (w->aux) {
-    (void)hipStreamSynchronize(w->aux);
-    (void)hipStreamDestroy(w->aux);
-  }
   if (w->e_next) (void)hipEventDestroy(w->e_next);
   if (w->e_rest) (void)hipEventDestroy(w->e_rest);
   pipe_destroy(w->pipe);
+  side_release(w->side);
   delete w;
 }
 
@@ -1183,14 +1248,6 @@ struct bm_lu_pipe {
 
 static void pipe_destroy(bm_lu_pipe *q) {
   if (!q) return;
-  if (q->g) {
-    (void)hipStreamSynchronize(q->g);
-    (void)hipStreamDestroy(q->g);
-  }
-  if (q->c) {
-    (void)hipStreamSynchronize(q->c);
-    (void)hipStreamDestroy(q->c);
-  }
   hipEvent_t *evs[] = {&q->e_in, &q->e_cdone};
   for (hipEvent_t *e : evs)
     if (*e) (void)hipEventDestroy(*e);
@@ -1204,15 +1261,16 @@ static void pipe_destroy(bm_lu_pipe *q) {
 }
 
 int bm_getrf_pipe_create(bm_getrf_ws *w) {
-  if (!w) return BM_E_ARG;
+  if (!w || !w->side) return BM_E_ARG;
   if (w->pipe) return BM_OK;
   bm_lu_pipe *q = new (std::nothrow) bm_lu_pipe();
   if (!q) return BM_E_NOMEM;
   memset((void *)q, 0, sizeof(*q));
   const unsigned fl = hipEventDisableTiming | BM_LU_EVENT_FLAGS;
-  bool ok = hipStreamCreateWithFlags(&q->g, hipStreamNonBlocking) == hipSuccess &&
-            hipStreamCreateWithFlags(&q->c, hipStreamNonBlocking) == hipSuccess &&
-            hipEventCreateWithFlags(&q->e_in, fl) == hipSuccess &&
+  bool ok = side_pipe_streams(w->side);
+  q->g = w->side->g;
+  q->c = w->side->c;
+  ok = ok && hipEventCreateWithFlags(&q->e_in, fl) == hipSuccess &&
             hipEventCreateWithFlags(&q->e_cdone, fl) == hipSuccess;
   for (int i = 0; ok && i < SP_MAXB; ++i) ok = hipEventCreateWithFlags(&q->ep[i], fl) == hipSuccess;
   for (int i = 0; ok && i < SP_MAXSEG; ++i)

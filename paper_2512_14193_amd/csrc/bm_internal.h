@@ -74,7 +74,8 @@ struct bm_getrf_ws {
   cplx *slots = nullptr;     // 2 buffers of per-column exchange records (candidates and diagonal row)
   int32_t *swp = nullptr;    // per panel: count, then (dst, src) pairs
   cplx *zbuf = nullptr;      // triangular solves: [ticket counters][lower solve's blocks][upper solve's blocks]
-  hipStream_t aux = nullptr;  // second stream: the trailing update of panel k runs beside panel k + 1
+  struct bm_lu_side *side = nullptr;  // the streams beside the problem's own, shared by the workspaces of its stream
+  hipStream_t aux = nullptr;  // one of them: the trailing update of panel k runs beside panel k + 1
   hipEvent_t e_next = nullptr, e_rest = nullptr;
   struct bm_problem *prof = nullptr;  // non-null: time each panel launch in that problem's BM_PH_PANEL phase
   struct bm_problem *prof_schur = nullptr;  // non-null: the segmented product's span in its BM_PH_SCHUR phase
@@ -341,7 +342,7 @@ int bm_launch_fds_targets(hipStream_t s, const bm_problem *p, int nitems, const 
                           cplx *out);
 
 // LU
-bm_getrf_ws *bm_getrf_ws_create(int n);
+bm_getrf_ws *bm_getrf_ws_create(int n, hipStream_t s);  // s: the stream the factorisations will run on
 void bm_getrf_ws_destroy(bm_getrf_ws *w);
 size_t bm_getrf_ws_bytes(int n);  // device bytes bm_getrf_ws_create(n) allocates
 // LU of A = alpha Bot Top (n x n; Bot n x k, Top k x n) with the product computed
