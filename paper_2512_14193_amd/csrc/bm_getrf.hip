@@ -163,7 +163,9 @@ __device__ inline cplx csel(bool c, cplx a, cplx b) { return cmk(c ? a.x : b.x, 
 
 // 1/u for the pivot: u scaled by the power of two that brings its larger component
 // into [1, 2) (built from the exponent bits: integer operations, on the path from one
-// pivot to the next), then conj(u) / |u|^2 with a Newton-refined hardware reciprocal
+// pivot to the next), then conj(u) / |u|^2 with a Newton-refined hardware reciprocal.
+// The scale comes back on conj(u) (beside the reciprocal's chain): 1/|u|^2 times it would
+// be denormal from |u| = 2^1020 on and infinite below 2^-1024, where 1/u still has its bits.
 __device__ inline cplx pivot_recip(cplx u) {
   const int ex = max(__double2hiint(u.x) & 0x7fffffff, __double2hiint(u.y) & 0x7fffffff) & 0x7ff00000;
   const double sc = __hiloint2double(0x7fe00000 - min(ex, 0x7fd00000), 0);
@@ -172,8 +174,7 @@ __device__ inline cplx pivot_recip(cplx u) {
   double r = __builtin_amdgcn_rcp(d);
   r = fma(r, fma(-d, r, 1.0), r);
   r = fma(r, fma(-d, r, 1.0), r);
-  r *= sc;
-  return cmk(us.x * r, -us.y * r);
+  return cmk(us.x * sc * r, -us.y * sc * r);
 }
 
 // Panel factorisation with split roles.  A workgroup holds RPW = 64 RPL rows of
