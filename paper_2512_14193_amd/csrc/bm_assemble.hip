@@ -24,14 +24,18 @@
 #include "bm_zeta_corr.h"
 
 // wide domain when a wavenumber lies below the sector |Im k| <= Re k / 2
-static bool bm_wide(const bm_phys &ph) { return ph.k0.y < -0.5 * ph.k0.x || ph.k1.y < -0.5 * ph.k1.x; }
+static int bm_domain(const bm_problem *p) {
+  const bm_phys &ph = p->phys;
+  if (ph.k0.y >= -0.5 * ph.k0.x && ph.k1.y >= -0.5 * ph.k1.x) return BM_DOM_SECTOR;
+  return (p->n <= BM_WIDE_SUM_MAX_N) ? BM_DOM_WIDE_SUM : BM_DOM_WIDE;
+}
 
 // The Hankel tables of the problem's wavenumbers (complex ones, and the wide domain),
 // after the quadrature weights.
 int bm_launch_hankel_rays(const bm_problem *p) {
   const bm_phys &ph = p->phys;
-  const bool wide = bm_wide(ph);
-  if (!wide && ph.k0.y == 0.0 && ph.k1.y == 0.0) return BM_OK;
+  const int dom = bm_domain(p);
+  if (dom == BM_DOM_WIDE_SUM || (dom == BM_DOM_SECTOR && ph.k0.y == 0.0 && ph.k1.y == 0.0)) return BM_OK;
   hipLaunchKernelGGL(hankel_ray_kernel, dim3(2), dim3(HK_RAY_NT), 0, p->stream, ph.k0, ph.k1,
                      (hk_ray *)(p->wts + 4 * (size_t)p->n));
   BM_HIP_TRY(hipGetLastError());
@@ -180,16 +184,17 @@ struct pair_k {
 };
 
 // The Hankel values at k r (real wavenumbers outside the wide domain need no table).
-template <bool WIDE>
+template <int DOM>
 __device__ inline bm_hk4 hankel_at(cplx k, const hk_ray *ray, double r, double rinv, bool *bad) {
-  if (!WIDE && k.y == 0.0) return bm_hankel01_real(k.x * r);
-  return bm_hankel01_ray<WIDE>(ray, r, rinv, bad);
+  if (DOM == BM_DOM_WIDE_SUM) return bm_hankel01_wide(cscale(k, r), bad);
+  if (DOM == BM_DOM_SECTOR && k.y == 0.0) return bm_hankel01_real(k.x * r);
+  return bm_hankel01_ray<DOM == BM_DOM_WIDE>(ray, r, rinv, bad);
 }
 
-template <bool WIDE>
+template <int DOM>
 __device__ inline pair_k pair_scalars(cplx k, const hk_ray *ray, double r, double rinv, double R, double L, double h,
                                       double a, double b, bool want_nu, bool *bad) {
-  const bm_hk4 hk = hankel_at<WIDE>(k, ray, r, rinv, bad);
+  const bm_hk4 hk = hankel_at<DOM>(k, ray, r, rinv, bad);
   pair_k o;
   // S: K = (i/4) H0, K1 = -J0/(4 pi)
   const cplx aS = cmk(-0.25 * hk.h0.y, 0.25 * hk.h0.x);
@@ -323,7 +328,7 @@ __device__ __forceinline__ void diag_entries(const asm_args &A, int i, cplx (&e)
   }
 }
 
-template <int FORM, bool WIDE>
+template <int FORM, int DOM>
 __global__ __launch_bounds__(256) void assemble_kernel(asm_args A) {
   // unordered tile pair (I, J), I <= J, from the triangular index
   const long Lt = blockIdx.x;
@@ -346,9 +351,9 @@ __global__ __launch_bounds__(256) void assemble_kernel(asm_args A) {
       const pair_geo g = pair_geometry(A, i, j);
       const double si = g.si, sj = g.sj, ndi = g.ndi, ndj = g.ndj, kap = g.kap;
       bool bad = false;
-      const pair_k p0 = pair_scalars<WIDE>(ph.k0, A.ray, g.r, g.rinv, g.R, g.L, A.h, g.a, g.b, true, &bad);
-      const pair_k p1 = pair_scalars<WIDE>(ph.k1, A.ray + 1, g.r, g.rinv, g.R, g.L, A.h, g.a, g.b, false, &bad);
-      if (WIDE && bad) atomicOr(A.dom_err, 1);
+      const pair_k p0 = pair_scalars<DOM>(ph.k0, A.ray, g.r, g.rinv, g.R, g.L, A.h, g.a, g.b, true, &bad);
+      const pair_k p1 = pair_scalars<DOM>(ph.k1, A.ray + 1, g.r, g.rinv, g.R, g.L, A.h, g.a, g.b, false, &bad);
+      if (DOM != BM_DOM_SECTOR && bad) atomicOr(A.dom_err, 1);
       // k0 operators at (i,j) and (j,i)
       const cplx S0ij = cscale(p0.sig, sj), S0ji = cscale(p0.sig, si);
       const cplx D0ij = cscale(p0.del, ndj), D0ji = cscale(p0.del, -ndi);
@@ -410,20 +415,18 @@ int bm_launch_assemble(bm_problem *p, const bm_geometry *g) {
   A.bot = p->bot;
   A.ord = p->lu;
   A.dom_err = p->dev_err + 2;
-  const bool wide = bm_wide(p->phys);
   if (int rc = bm_launch_hankel_rays(p)) return rc;
   if (int rc = bm_fill_u64(p->stream, p->dev_err + 2, 1, 0ull)) return rc;  // words 2, 3
   const long nt = (p->n + ASM_TB - 1) / ASM_TB;
   const long ntiles = nt * (nt + 1) / 2;
   const dim3 grid((unsigned)ntiles);
-  if (p->form == BM_MIXED && !wide)
-    hipLaunchKernelGGL((assemble_kernel<BM_MIXED, false>), grid, dim3(256), 0, p->stream, A);
-  else if (p->form == BM_MIXED)
-    hipLaunchKernelGGL((assemble_kernel<BM_MIXED, true>), grid, dim3(256), 0, p->stream, A);
-  else if (!wide)
-    hipLaunchKernelGGL((assemble_kernel<BM_ORDINARY, false>), grid, dim3(256), 0, p->stream, A);
-  else
-    hipLaunchKernelGGL((assemble_kernel<BM_ORDINARY, true>), grid, dim3(256), 0, p->stream, A);
+  typedef void (*assemble_fn)(asm_args);
+  static const assemble_fn fns[2][3] = {  // by formulation and BM_DOM_*
+      {assemble_kernel<BM_MIXED, BM_DOM_SECTOR>, assemble_kernel<BM_MIXED, BM_DOM_WIDE>,
+       assemble_kernel<BM_MIXED, BM_DOM_WIDE_SUM>},
+      {assemble_kernel<BM_ORDINARY, BM_DOM_SECTOR>, assemble_kernel<BM_ORDINARY, BM_DOM_WIDE>,
+       assemble_kernel<BM_ORDINARY, BM_DOM_WIDE_SUM>}};
+  hipLaunchKernelGGL(fns[p->form == BM_MIXED ? 0 : 1][bm_domain(p)], grid, dim3(256), 0, p->stream, A);
   BM_HIP_TRY(hipGetLastError());
   return BM_OK;
 }
@@ -571,10 +574,10 @@ __device__ cplx mixed_entry(const asm_args &A, int tr, int i, int tc, int j) {
   const pair_geo g = pair_geometry(A, i, j);
   bool bad = false;
   if (blk < 2) {
-    const pair_k p1 = pair_scalars<false>(ph.k1, A.ray + 1, g.r, g.rinv, g.R, g.L, A.h, g.a, g.b, false, &bad);
+    const pair_k p1 = pair_scalars<BM_DOM_SECTOR>(ph.k1, A.ray + 1, g.r, g.rinv, g.R, g.L, A.h, g.a, g.b, false, &bad);
     return blk == 0 ? cscale(p1.sig, -g.sj) : cscale(p1.del, g.ndi * g.sj / (g.si * ph.eps1));
   }
-  const pair_k p0 = pair_scalars<false>(ph.k0, A.ray, g.r, g.rinv, g.R, g.L, A.h, g.a, g.b, blk == 2, &bad);
+  const pair_k p0 = pair_scalars<BM_DOM_SECTOR>(ph.k0, A.ray, g.r, g.rinv, g.R, g.L, A.h, g.a, g.b, blk == 2, &bad);
   if (blk == 2) {
     const cplx N0 = cadd(cmk(g.kap / g.si, 0.0), cscale(p0.nu, g.sj));
     return cadd(cscale(p0.del, g.ndj), cmul(ph.beta, N0));
@@ -593,7 +596,7 @@ __device__ inline pt_k point_kernels(cplx k, const hk_ray *ray, double2 x, doubl
   const double d1 = x.x - y.x, d2 = x.y - y.y;
   const double r2 = d1 * d1 + d2 * d2, r = sqrt(r2), rinv = 1.0 / r;
   bool bad = false;
-  const bm_hk4 hk = hankel_at<false>(k, ray, r, rinv, &bad);
+  const bm_hk4 hk = hankel_at<BM_DOM_SECTOR>(k, ray, r, rinv, &bad);
   const double nxd = nx.x * d1 + nx.y * d2, nyd = ny.x * d1 + ny.y * d2, a = nx.x * ny.x + nx.y * ny.y;
   const cplx ik4 = cmk(-0.25 * k.y, 0.25 * k.x);
   pt_k o;

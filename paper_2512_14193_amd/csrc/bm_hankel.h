@@ -33,6 +33,10 @@
 // (the last term is below 1e-26 of the largest); in the lower half plane J and Y grow
 // like H^(1), so the series loses at most a factor e^{|z| - |Im z|} <= 30 to
 // cancellation.  Larger |z| is outside the supported domain: the caller flags it.
+// Up to BM_WIDE_SUM_MAX_N nodes each pair sums its own terms: the tables' kernel and
+// their loads, 18 and 9 us, are then more than they save.  Assembly by pairs and by
+// tables: N = 128 22 and 48 us, 512 34 and 54, 1024 66 and 69, 1100 72 and 71,
+// 1400 105 and 84, 2048 198 and 131 (both formulations alike).
 #pragma once
 
 #include "bm_internal.h"
@@ -132,9 +136,61 @@ __device__ inline bm_hk4 bm_hankel01_real(double x) {
   return o;
 }
 
+// How the Hankel values of an assembly are evaluated
+enum {
+  BM_DOM_SECTOR,    // wavenumbers in the sector
+  BM_DOM_WIDE,      // the wide domain, by tables
+  BM_DOM_WIDE_SUM,  // the wide domain, each pair its own sum
+};
+#define BM_WIDE_SUM_MAX_N 1024
+#define BM_WIDE_ZMAX 6.0  // largest |z| of the wide domain
+
+// The power series at complex z (NT terms)
+template <int NT>
+__device__ inline void bm_hankel_sum(cplx z, bm_hk4 &o) {
+  const cplx mw = cscale(cmul(z, z), -0.25);  // -z^2/4
+  cplx t0 = cmk(1.0, 0.0), t1 = cmk(1.0, 0.0);
+  cplx sj0 = cmk(0, 0), sj1 = cmk(0, 0), sy0 = cmk(0, 0), sy1 = cmk(0, 0);
+  double hk = 0.0, hk1 = 1.0;  // harmonic numbers H_k, H_{k+1}
+#pragma unroll
+  for (int k = 0; k < NT; ++k) {
+    sj0 = cadd(sj0, t0);
+    sj1 = cadd(sj1, t1);
+    sy0 = cadd(sy0, cscale(t0, hk));
+    sy1 = cadd(sy1, cscale(t1, hk + hk1));
+    t0 = cscale(cmul(t0, mw), 1.0 / ((k + 1.0) * (k + 1.0)));
+    t1 = cscale(cmul(t1, mw), 1.0 / ((k + 1.0) * (k + 2.0)));
+    hk = hk1;
+    hk1 += 1.0 / (k + 2.0);
+  }
+  const cplx zh = cscale(z, 0.5);
+  const cplx J0 = sj0, J1 = cmul(zh, sj1);
+  cplx L = clog_d(zh);
+  L.x += BM_EULER;
+  const cplx Y0 = cscale(csub(cmul(L, J0), sy0), 2.0 / BM_PI);
+  const cplx Y1 = cadd(cadd(cscale(crecip(z), -2.0 / BM_PI), cscale(cmul(L, J1), 2.0 / BM_PI)),
+                       cscale(cmul(zh, sy1), -1.0 / BM_PI));
+  o.j0 = J0;
+  o.j1 = J1;
+  o.h0 = cmk(J0.x - Y0.y, J0.y + Y0.x);
+  o.h1 = cmk(J1.x - Y1.y, J1.y + Y1.x);
+}
+
+// The wide domain without tables; *bad is set when |z| >= BM_WIDE_ZMAX.
+__device__ inline bm_hk4 bm_hankel01_wide(cplx z, bool *bad) {
+  bm_hk4 o;
+  const double az2 = cabs2(z);
+  if (az2 < 9.0) {
+    bm_hankel_sum<18>(z, o);
+  } else {
+    if (!(az2 < BM_WIDE_ZMAX * BM_WIDE_ZMAX)) *bad = true;
+    bm_hankel_sum<26>(z, o);
+  }
+  return o;
+}
+
 // Tables of one wavenumber k = ak e^{i th} (hankel_ray_kernel); every lane reads the
 // same entries, so they come through the scalar cache.
-#define BM_WIDE_ZMAX 6.0  // largest |z| of the wide domain
 #define HK_NS 26          // series terms (18 for |z| < 3)
 #define HK_NC 28          // Chebyshev coefficients (those of degree 24 and beyond are below 1e-16)
 struct hk_ray {
