@@ -183,13 +183,15 @@ int bm_block_lu(bm_problem *p, int32_t *info);
  * together: each Schur complement as in bm_block_lu (U33 formed in full before its
  * LU), then one LU in which every panel, interchange and update launch covers all
  * of the problems, so that the CUs one problem's panel chain leaves idle serve the
- * others (the panels of the batch together need count * ceil(N / 64) workgroups
- * resident, at most the CU count).  Each problem gets bitwise the factors that
+ * others (a panel has 16 workgroups for N of 65 to 2688, up to 8 below and
+ * ceil(N / 128) above, each on a CU of its own; problems whose panels the CUs do
+ * not hold together are factored in parts).  Each problem gets bitwise the factors that
  * bm_block_lu without the segmented product gives it (in mixed precision, the
  * complex64 factors of its FP32 factorisation).  info: NULL (asynchronous) or a host
  * array of count entries, filled as bm_block_lu's (then it waits).
  * Errors: BM_E_ARG (count, differing N, precision, device or stream, a repeated or
- * ordinary problem, too many panel workgroups), BM_E_STATE. */
+ * ordinary problem, count * ceil(N / 64) above the CU count, ceil(N / 128) from
+ * N = 2050 on), BM_E_STATE. */
 #define BM_LU_BATCH_MAX 4
 int bm_block_lu_batch(bm_problem *const *ps, int32_t count, int32_t *info);
 
@@ -389,8 +391,9 @@ int bm_problem_bytes(int32_t n, int32_t formulation, int64_t *bytes);
  *     HIP graph captured once per handle (the host cost of a small request is
  *     its kernel launches); results are bitwise identical to the eager path.
  * Concurrency is limited to small problems because the panel factorisation
- * needs all of its workgroups resident at once: the panels of all lanes fit
- * beside each other (lanes * ceil(concurrent_max_n / 64) <= CUs / 2) and the
+ * needs all of its workgroups (16, see bm_block_lu_batch) resident at once: small
+ * requests use as many lanes as keep the panels of all of them within half of the
+ * CUs (8 of 256 CUs, 16 where concurrent_max_n <= 64), and the
  * kernels of small requests are short, whereas a large request's Schur
  * complement occupies every CU for tens of milliseconds.  A request's result
  * does not depend on the other requests (bitwise).  Mixed formulation, FP64 or
@@ -407,7 +410,8 @@ typedef struct {
   int32_t lanes;             /* concurrent streams, 1..16; 0: 4                    */
   int32_t concurrent_max_n;  /* N up to which requests share the device; 0: 1024;
                                 with lanes > 1 it must be <= 2048 and
-                                lanes * ceil(concurrent_max_n / 64) <= CUs / 2      */
+                                lanes * ceil(concurrent_max_n / 64) <= CUs / 2 (of
+                                more than 8 lanes such requests use 8, see above)    */
   int32_t quadrature;        /* BM_QUAD_* of every handle (0: Kress)                 */
   int32_t precision;         /* BM_PREC_FP64 (0) or BM_PREC_MIXED_DEVICE: the FP32
                                 Schur complement with refinement decided on the
@@ -419,9 +423,9 @@ typedef struct {
                                 (<= BM_LU_BATCH_MAX, no reuse key) are factored
                                 together on one lane (bm_block_lu_batch), as many
                                 as their panels fit a lane's share of the panel
-                                workgroups, CUs / 2 / lanes: at N = 1024 two with
-                                4 lanes, four with 2.  Each gets bitwise its own
-                                factors.  <= 1: one at a time                      */
+                                workgroups, CUs / 2 / lanes: two with 4 lanes, four
+                                with 2 (twice that for N <= 64).  Each gets bitwise
+                                its own factors.  <= 1: one at a time              */
 } bm_server_config;
 
 /* One request.  Device arrays: the geometry (as bm_assemble), B (3N x nrhs,

@@ -46,14 +46,7 @@
 // no counter, one round trip per column (a reader takes the headers, then the
 // winner's row and the diagonal row, written right after the header).
 // ---------------------------------------------------------------------------
-#define PANEL_PMAX 256            // max workgroups of a panel launch
 #define SENT 0xFFFFFFFFFFFFFFFFULL  // empty exchange word (all ones)
-#define SNT 448                   // threads per panel workgroup: one chain + SNB bulk wavefronts
-#define SNB 6
-// LDS requested by every panel launch: more than 160 KB minus any GEMM workgroup's
-// share, so that no workgroup of the concurrent trailing update lands on a CU that
-// runs a panel workgroup (the chain would lose issue slots)
-#define PANEL_LDS_ALLOC ((size_t)LU_NB * (128 + 1) * sizeof(cplx))
 
 // Slot buffer layout: per column c, the P records of rec = jb + 1 complex values
 // (candidate row, then its value and row index) followed by the diagonal row, and,
@@ -862,7 +855,6 @@ using panel_fn = void (*)(int, T *, long, int, int, int, int32_t *, int32_t *, c
                           bm_lu_batch);
 // By kind of panel (lu_shape): the streaming panels by rows per thread and columns
 // per workgroup, then the exchanging panel.
-#define PANEL_KINDS 6
 template <class T, bool BAT>
 static panel_fn<T> panel_fn_of(int kind) {
   static const panel_fn<T> fns[PANEL_KINDS] = {
@@ -888,55 +880,6 @@ int bm_fill_u64(hipStream_t s, void *p, size_t n, unsigned long long v) {
   hipLaunchKernelGGL(fill_u64_kernel, dim3((unsigned)nb), dim3(256), 0, s, (unsigned long long *)p, n, v);
   BM_HIP_TRY(hipGetLastError());
   return BM_OK;
-}
-
-// How the panel of R rows and jb columns runs: kind of kernel (panel_fn_of), its
-// workgroups, and the exchange words it uses (slots_refill).  The streaming panel
-// holds (rows per thread) x (columns per workgroup) values in a thread's registers.
-// Per 64-column panel (us, alone on the device; threads x rows per thread x columns
-// per workgroup):
-//   rows      streaming                            exchanging (64 or 128 rows/workgroup)
-//     64       47 (64x1x8)                          135
-//    512       60 (256x2x4), 65 (512x1x4)           130
-//   1024       72 (512x2x4), 77 (x8), 76 (256x4x4)  130
-//   2048       94 (512x4x4), 108 (x2), 125 (1024x2x4)  131 to 155
-//   2688      119 (448x6x4)                         150
-//   3136      306 (448x8x4, spilled)                151
-//   4032      167 (512x8x4), 200 (448x9x2)          152
-// A thread of 512 or fewer holds 256 registers, which six rows of four columns fill with
-// the next column's multipliers on their way.  Beyond 2688 rows they cannot be on their
-// way, or a workgroup holds two columns, and reading the earlier columns becomes the
-// chain: the exchanging panel (128 rows per workgroup) takes over.
-struct lu_shape {
-  int kind, wgs, threads, fill_h;
-  long fill_n;
-  size_t lds;
-};
-#define PANEL_STREAM_MAX_R 2688
-static bool panel_shape(int R, int jb, int ncu, lu_shape *o) {
-  // (the exchanging panel's workgroup count bounds the orders taken, whichever runs)
-  const int pmax = (ncu < PANEL_PMAX) ? ncu : PANEL_PMAX;
-  const int P = (R + 127) / 128;
-  if (P < 1 || ((R > 2048) ? P : (R + 63) / 64) > pmax) return false;
-  if (R <= PANEL_STREAM_MAX_R) {
-    static const int cw[PANEL_KINDS - 1] = {8, 4, 4, 4, 4}, nt[PANEL_KINDS - 1] = {64, 256, 512, 512, 448};
-    int k = (R <= LU_NB) ? 0 : 1;
-    while (k > 0 && R > (256 << k)) ++k;
-    o->kind = k;
-    o->wgs = (jb + cw[k] - 1) / cw[k];
-    o->threads = nt[k] + 64;
-    o->lds = SPN_LDS_ALLOC;
-    o->fill_n = (long)jb * R;
-    o->fill_h = jb;
-  } else {
-    o->kind = PANEL_KINDS - 1;
-    o->wgs = P;
-    o->threads = SNT;
-    o->lds = PANEL_LDS_ALLOC;
-    o->fill_n = (long)jb * ((long)P * (jb + 1) + jb);
-    o->fill_h = jb * P;
-  }
-  return true;
 }
 
 size_t bm_getrf_ws_bytes(int n) {
@@ -1047,8 +990,8 @@ static int lu_begin(hipStream_t s, int n, int32_t *dev_err, bm_getrf_ws *w, lu_s
   return BM_OK;
 }
 
-// Launch of panel pi (all P workgroups must run at the same time: P <= the CU
-// count, checked in panel_shape, and one workgroup fits a CU, so on a device that
+// Launch of panel pi (all of its workgroups must run at the same time: there are no
+// more of them than CUs, and one workgroup fits a CU, so on a device that
 // is not saturated by other work every workgroup is resident at once; a plain
 // launch avoids the start and drain cost of a cooperative launch.  Every wait in
 // the kernel is bounded, so a launch whose workgroups cannot all become resident
@@ -1161,11 +1104,21 @@ static int getrf_run_batch(hipStream_t s, int n, int count, T *const *A, int64_t
   for (int b = 0; b < count; ++b)
     if (!ws[b] || ws[b]->n < n || !A[b] || !ipiv[b] || !dev_err[b]) return BM_E_ARG;
   lu_shape shape[1024];
-  int ncu = 0;
+  int dev = 0, ncu = 0;
+  BM_HIP_TRY(hipGetDevice(&dev));
+  BM_HIP_TRY(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
+  // every workgroup of a batched panel must be resident at once: in parts where the
+  // device does not hold the panels of all of them
+  const int fit = lu_batch_fit(n, count, ncu);
+  if (fit < 1) return BM_E_ARG;
+  if (fit < count) {
+    for (int b = 0; b < count; b += fit)
+      if (int rc = getrf_run_batch(s, n, (count - b < fit) ? count - b : fit, A + b, lda, ipiv + b, dev_err + b, ws + b))
+        return rc;
+    return BM_OK;
+  }
   for (int b = 0; b < count; ++b)  // per problem: flags and the first panel's exchange words
     if (int rc0 = lu_begin(s, n, dev_err[b], ws[b], shape, &ncu)) return rc0;
-  // every workgroup of a batched panel must be resident at once
-  if ((long)count * ((n > 2048) ? (n + 127) / 128 : (n + 63) / 64) > ncu) return BM_E_ARG;
   bm_getrf_ws *w = ws[0];
   const bool la = w->aux != nullptr;
   bm_lu_batch bb{};

@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "../../include/bm.h"
+#include "bm_lu_rules.h"
 
 typedef double2 cplx;  // (re, im), the layout of torch.complex128
 typedef float2 cplx32;  // (re, im), the layout of torch.complex64: storage of the FP32 factorisation
@@ -65,7 +66,6 @@ __device__ inline cplx csqrt_d(cplx w) {
 // ---------------------------------------------------------------------------
 // factorisation workspace and cross-workgroup helpers
 // ---------------------------------------------------------------------------
-#define LU_NB 64                   // LU panel width
 #define BM_DIAG_NB 64              // block size of the triangular solves
 #define SWP_STRIDE (1 + 4 * LU_NB) // per panel: count, then (dst, src) row pairs
 

@@ -84,8 +84,6 @@ __device__ __forceinline__ double row_bcast_at(double v, int i) {
   }
 }
 
-#define SPN_LDS_ALLOC ((size_t)120 * 1024)  // dynamic LDS of a launch (see PANEL_LDS_ALLOC)
-
 template <int NT, int RPT, int CW, class T, bool BAT>
 __global__ __launch_bounds__(NT + 64) void panel_stream_kernel(int N, T *A, long lda, int j, int jb_, int G,
                                                                int32_t *ipiv, int32_t *dev_err, cplx *slots,

@@ -12,13 +12,14 @@
 // ahead, so the device never waits for the host.  (The lanes' streams only run
 // side by side if the process has enough hardware queues: GPU_MAX_HW_QUEUES.)
 //
-// Why concurrency is limited to small problems: the panel factorisation needs
-// its P workgroups resident at once (P = ceil(rows / 64) <= 16 for N <= 1024).
-// With lanes * P <= CUs / 2 every panel of every lane fits beside the others,
-// and each kernel of a small request is short (well under a millisecond at
-// N <= 1024), so a panel workgroup waits at most that long for a free CU.  A
-// large request's Schur complement GEMM occupies every CU for tens of
-// milliseconds, which could hold off another lane's panel for as long.
+// Why concurrency is limited to small problems: the panel factorisation needs its
+// workgroups resident at once (16 for 65 to 2688 rows, each on a CU of its own).
+// Small requests use as many lanes as keep the panels of all of them, with the
+// requests that a lane factors together, within half of the CUs; so every panel of
+// every lane fits beside the others, and each kernel of a small request is short
+// (well under a millisecond at N <= 1024), so a panel workgroup waits at most that
+// long for a free CU.  A large request's Schur complement GEMM occupies every CU for
+// tens of milliseconds, which could hold off another lane's panel for as long.
 #include <math.h>
 #include <string.h>
 
@@ -87,6 +88,7 @@ struct bm_server {
   int max_inflight = 4;        // per lane
   int graph_max_n = 0;
   int concurrent_max_n = 0;
+  int small_lanes = 1;     // lanes that requests with N <= concurrent_max_n use
   int batch_max = 1;       // requests of one N factored together (FP64)
   int ncu = 0;
   int quad = BM_QUAD_KRESS;    // quadrature of every handle
@@ -140,27 +142,20 @@ void release_handle(srv_handle *h) {
 }
 
 bool is_small(const bm_server *s, int n) { return s->lanes.size() > 1 && n <= s->concurrent_max_n; }
-// workgroups of the widest panel of an N-node factorisation (64 rows each up to
-// 32 workgroups, then 128)
-int panel_p(int n) { return (n <= 64 * 32) ? (n + 63) / 64 : (n + 127) / 128; }
-// requests of N nodes that may be factored together: their panels within one
-// lane's share of the panel workgroups all lanes may hold, half the CUs
+// requests of N nodes that may be factored together
 int batch_limit(const bm_server *s, int n) {
-  if (s->batch_max < 2 || !is_small(s, n)) return 1;
-  const int fit = (s->ncu / 2 / (int)s->lanes.size()) / panel_p(n);
-  const int b = (s->batch_max < fit) ? s->batch_max : fit;
-  return (b < BM_LU_BATCH_MAX) ? (b > 1 ? b : 1) : BM_LU_BATCH_MAX;
+  return is_small(s, n) ? srv_batch_limit(n, s->batch_max, s->small_lanes, s->ncu) : 1;
 }
 
 // Lane for a request: the lane that holds its keyed factors, else the least
-// loaded lane for a small request, else lane 0.
+// loaded of the lanes for small requests, else lane 0.
 int choose_lane(const bm_server *s, const bm_request &r) {
   if (r.reuse_key != 0)
     for (const srv_handle *h : s->handles)
       if (h->n == r.n && h->key == r.reuse_key) return h->lane;
   if (!is_small(s, r.n)) return 0;
   int best = 0;
-  for (int l = 1; l < (int)s->lanes.size(); ++l)
+  for (int l = 1; l < s->small_lanes; ++l)
     if (s->lanes[l].inflight < s->lanes[best].inflight) best = l;
   return best;
 }
@@ -576,8 +571,7 @@ int bm_server_create(const bm_server_config *cfg, bm_server **out) {
   int dev = 0, ncu = 0;
   if (hipGetDevice(&dev) != hipSuccess) return BM_E_HIP;
   if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return BM_E_HIP;
-  // the panels of all lanes together may take at most half of the CUs
-  if (lanes > 1 && (cmax > 2048 || lanes * ((cmax + 63) / 64) > ncu / 2)) return BM_E_ARG;
+  if (!srv_lanes_ok(lanes, cmax, ncu)) return BM_E_ARG;
   bm_server *s = new (std::nothrow) bm_server();
   if (!s) return BM_E_NOMEM;
   s->device = dev;
@@ -585,6 +579,7 @@ int bm_server_create(const bm_server_config *cfg, bm_server **out) {
   s->graph_max_n = c.graph_max_n;
   s->concurrent_max_n = cmax;
   s->ncu = ncu;
+  s->small_lanes = srv_small_lanes(lanes, cmax, ncu);
   s->batch_max = (c.batch_max < 1) ? 1 : ((c.batch_max > BM_LU_BATCH_MAX) ? BM_LU_BATCH_MAX : c.batch_max);
   s->quad = c.quadrature;
   s->prec = c.precision;
