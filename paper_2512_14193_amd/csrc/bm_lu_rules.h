@@ -105,3 +105,99 @@ static inline int srv_batch_limit(int n, int batch_max, int small_lanes, int ncu
   const int b = (batch_max < fit) ? batch_max : fit;
   return (b < 1) ? 1 : b;
 }
+
+// ---------------------------------------------------------------------------
+// The segments of the product beside the panels (bm_getrf_schur_run)
+// ---------------------------------------------------------------------------
+#define SP_MAXSEG 10
+
+struct sp_seg {
+  int b0, b1, ks;  // blocks [b0, b1), k split into ks slices
+};
+
+// k-slices of a product of `tiles` tiles on `slots` workgroups: enough to fill
+// them in one round, at most 16, each at least 256 deep (the three-multiplication
+// form), and the partials within the workspace
+static inline int sp_ksplit(int tiles, int slots, int k, size_t w_cap) {
+  int ks = (tiles <= slots) ? slots / tiles : 1;
+  const int kmax = (k / 256 > 1) ? k / 256 : 1;
+  if (ks > kmax) ks = kmax;
+  if (ks > 16) ks = 16;
+  while (ks > 1 && (size_t)ks * tiles * 64 * 64 > w_cap) --ks;
+  return ks < 1 ? 1 : ks;
+}
+
+static inline double sp_time(int tiles, int ks, int slots, int k, double per_k) {
+  int kc = (k + ks - 1) / ks;
+  kc = (kc + 15) / 16 * 16;
+  const int rounds = (tiles * ks + slots - 1) / slots;
+  return rounds * per_k * kc + (ks > 1 ? 0.006 : 0.0);
+}
+
+// per_k1, per_k2: ms per unit of k of a round of tiles, one workgroup per CU and two
+// (block 0, whole device).  Returns 1 when, with a panel of the chain taking beta ms, the
+// planned product has at most SP_MAXSEG segments and ends before the chain of panels (the
+// overlap pays), else 0 (then the product is better formed in full first).
+static inline int sp_plan_at(double beta, double per_k1, double per_k2, int n, int k, int ncu, int gs, size_t w_cap,
+                             sp_seg *seg, int *nseg_out) {
+  const int B = (n + LU_NB - 1) / LU_NB, tb = B;  // blocks; row tiles of a block
+  const double margin = 0.03;
+  int nseg = 0;
+  const int ks0 = sp_ksplit(tb, 2 * ncu, k, w_cap);
+  const double t0 = sp_time(tb, ks0, 2 * ncu, k, per_k2);
+  seg[nseg++] = {0, 1, ks0};
+  double E = t0;
+  int f = 1;
+  while (f < B) {
+    if (nseg == SP_MAXSEG) return 0;
+    const double limit = t0 + beta * f - margin, least = tb * per_k1 * k / gs;  // least: ms a block, all slots busy
+    int best = 1, bks = sp_ksplit(tb, gs, k, w_cap);
+    double bt = sp_time(tb, bks, gs, k, per_k1);
+    for (int b = 2; b <= B - f && E + b * least <= limit + 1e-6; ++b) {
+      const int ks = sp_ksplit(tb * b, gs, k, w_cap);
+      const double t = sp_time(tb * b, ks, gs, k, per_k1), fin = E + t;
+      int a = (int)((fin - t0) / beta);
+      if (a > f - 1) a = f - 1;
+      if (a < 0) a = 0;
+      const double step = 0.012 + 8.0 * n * (64.0 * b) * 64.0 / 25e9;
+      if (fin + a * step <= limit) {
+        best = b;
+        bks = ks;
+        bt = t;
+      }
+    }
+    // a segment that would leave a single block, which alone would need a catch-up
+    // step for every panel before it, takes the rest
+    if (B - f - best == 1 && nseg >= 2) {
+      best = B - f;
+      bks = sp_ksplit(tb * best, gs, k, w_cap);
+      bt = sp_time(tb * best, bks, gs, k, per_k1);
+    }
+    seg[nseg++] = {f, f + best, bks};
+    E += bt;
+    f += best;
+  }
+  *nseg_out = nseg;
+  return (E <= t0 + beta * B - margin) ? 1 : 0;
+}
+
+// The plan for the shortest panel time that needs few segments.  A panel with the
+// launches to the next one takes 0.09 to 0.12 ms, but each segment's catch-up steps slow
+// the chain in ways the model leaves out, so a plan of many segments loses what it gains
+// (n = 1728: 9 segments 3.41 ms, 14 segments 4.30, 7 segments 3.74, product first 4.23;
+// n = 2048: 9 segments 4.72, 13 segments 5.45, 24 segments 7.35, product first 5.20).
+// First with the product an eighth slower than it runs alone, which leaves it room beside
+// the updates (n = 1728: 3.25 ms, planned at its own rate 3.50), then, where that finds
+// none, at its own rate and with the panels of more than 2048 rows in mind, 0.12 to 0.15 ms
+// and the launches (product first -> beside the panels: n = 2176 5.77 -> 5.18 ms,
+// 2240 6.00 -> 5.81, 2368 6.88 -> 6.41, 2432 7.12 -> 6.78; from about 2460 on no plan is
+// found).  Every factorisation plans anew: a plan is given up at its eleventh segment and
+// a segment's widths are tried up to the bound, 1 to 3 us on the host in all (with every
+// plan and width tried to the end 12 us at n = 2048 and 110 at 4096).
+static inline int sp_plan(int n, int k, int ncu, int gs, size_t w_cap, sp_seg *seg, int *nseg_out) {
+  for (int i = 0; i <= 4; ++i)
+    if (sp_plan_at(0.09 + 0.015 * i, 0.49 / 4096, 0.84 / 4096, n, k, ncu, gs, w_cap, seg, nseg_out)) return 1;
+  for (int i = 0; i <= 7; ++i)
+    if (sp_plan_at(0.09 + 0.015 * i, 0.43 / 4096, 0.74 / 4096, n, k, ncu, gs, w_cap, seg, nseg_out)) return 1;
+  return 0;
+}
