@@ -318,17 +318,15 @@ __global__ __launch_bounds__(NT + 64) void panel_stream_kernel(int N, T *A, long
     } else {
       load();
       // columns of the earlier workgroups, as they arrive
-      constexpr bool AHEAD = RPT < 16;  // (16 rows leave no registers to load a column ahead)
       bm_v4i hw, lw[RPT];
       auto fetch = [&](int t) __attribute__((always_inline)) {
         hw = header(t);
 #pragma unroll
         for (int k = 0; k < RPT; ++k) lw[k] = word(off[k], t);
       };
-      if (AHEAD && nst > 0) fetch(0);
+      if (nst > 0) fetch(0);
 #pragma unroll 1
       for (int t = 0; t < nst; ++t) {
-        if (!AHEAD) fetch(t);
         unsigned long long t0 = 0;
         for (;;) {
           bool need = rec_empty(hw);
@@ -344,7 +342,7 @@ __global__ __launch_bounds__(NT + 64) void panel_stream_kernel(int N, T *A, long
         st_v2 l[RPT];
 #pragma unroll
         for (int k = 0; k < RPT; ++k) l[k] = to_v2(rec_value(lw[k]));
-        if (AHEAD && t + 1 < nst) fetch(t + 1);
+        if (t + 1 < nst) fetch(t + 1);
         // the pivot row's entries of these columns, from the thread that holds the row
         if (slot >= 0)
           retire(slot, [&](int k) __attribute__((always_inline)) {
