@@ -38,7 +38,8 @@ TRAFFIC = {
                    (("bm_zgemm.hip", None, "// Persistent form of the deep product"),), False),
     "panel": ("panel_star2048_traffic.json",
               (("bm_getrf.hip", "// 1. panel factorisation", "// 2. row interchanges outside the panel"),
-               ("bm_internal.h", None, None)), True),
+               ("bm_panel_stream.h", None, None), ("bm_lu_rules.h", None, None), ("bm_internal.h", None, None)),
+              True),
 }
 
 
