@@ -187,9 +187,9 @@ __device__ inline cplx pivot_recip(cplx u) {
 //   wavefronts 1 .. SNB: subtract l_r u_cc from columns cc >= c + 3 and count
 //   themselves done; wavefront 0 waits for that count before it writes rows or
 //   reads columns of the next step.
-// Exchange layout per column c (rs = record stride, cstride = complex values per column):
-//   slots[c * cstride + g * rs]  record of workgroup g: (value, row), then the row
-//   slots[c * cstride + P * rs]  the diagonal row j + c, by its owner
+// Exchange layout per column c (rec: complex values per record, cstride: per column):
+//   slots[c * cstride + g * rec]  record of workgroup g: (value, row), then the row
+//   slots[c * cstride + P * rec]  the diagonal row j + c, by its owner
 //   slots[SLOT_HDR + c * P + g]  the header (value, row) of workgroup g when packed
 // (BAT: a batch of problems, blockIdx.y selecting the problem's matrix, pivots,
 // flags, exchange slots and interchange list from bb)
@@ -214,13 +214,8 @@ __global__ __launch_bounds__(SNT) void panel_kernel(int N, T *A, long lda, int j
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = (int)blockIdx.x;
   const int rec = jb + 1;
-  const int rstr = rec;
   const int cstride = P * rec + jb;
   const __amdgpu_buffer_rsrc_t rs = rec_rsrc(slots);
-  // element of the header of workgroup t for column cc
-  auto hdr_el = [&](int cc, int t) __attribute__((always_inline)) {
-    return SLOT_HDR + cc * P + t;
-  };
   const long r0 = (long)j + (long)g * RPW;  // first row of the workgroup
   const int nv = (N - r0 >= RPW) ? RPW : ((N - r0 > 0) ? (int)(N - r0) : 0);
   bool ok = true;
@@ -273,13 +268,13 @@ __global__ __launch_bounds__(SNT) void panel_kernel(int N, T *A, long lda, int j
     };
     // records of column cc: the header (value, row) as soon as the candidate is known
     auto publish_head = [&](int cc, double v, int lr) __attribute__((always_inline)) {
-      if (lane == 0) rec_store(rs, hdr_el(cc, g), (lr >= 0) ? cmk(v, (double)(r0 + lr)) : cmk(-1.0, -1.0));
+      if (lane == 0) rec_store(rs, SLOT_HDR + cc * P + g, (lr >= 0) ? cmk(v, (double)(r0 + lr)) : cmk(-1.0, -1.0));
     };
     // then (for column 0) the candidate row lr and the diagonal row; columns > cc
     // still owe the update of pivot cc - 1 (multipliers in column cc - 1, pivot row pr)
     auto publish_rows = [&](int cc, int lr, cplx pr) __attribute__((always_inline)) {
       const int base = cc * cstride;
-      const int sc = base + g * rstr;
+      const int sc = base + g * rec;
       const bool late = (cc > 0) && lane > cc;
       const long ld = (long)j + cc - r0;
       const bool has_d = (ld >= 0 && ld < nv);
@@ -293,7 +288,7 @@ __global__ __launch_bounds__(SNT) void panel_kernel(int N, T *A, long lda, int j
         if (late) y = cfms(y, pan[(cc - 1) * LDP + (int)ld], pr);
       }
       if (col_ok) rec_store(rs, sc + 1 + lane, x);  // zeros when the workgroup has no candidate
-      if (col_ok && has_d) rec_store(rs, base + P * rstr + lane, y);
+      if (col_ok && has_d) rec_store(rs, base + P * rec + lane, y);
     };
     cplx xc[RPL], xn[RPL];  // columns c and c + 1 of the workgroup's rows
 #pragma unroll
@@ -317,7 +312,7 @@ __global__ __launch_bounds__(SNT) void panel_kernel(int N, T *A, long lda, int j
       const int base = c * cstride;
       // receive the headers (lanes < P)
       bm_v4i vh;
-      const int eh = (lane < P) ? hdr_el(c, lane) : -1;
+      const int eh = (lane < P) ? SLOT_HDR + c * P + lane : -1;
       if (eh >= 0) vh = rec_load(rs, eh);
       {
         const unsigned long long t0 = wall_clock64();
@@ -349,12 +344,12 @@ __global__ __launch_bounds__(SNT) void panel_kernel(int N, T *A, long lda, int j
       } else {
         // more than 64 workgroups: the headers again through the record buffer
         double lv = -1.0;
-        for (int t = lane; t < P; t += 64) lv = fmax(lv, rec_poll(rs, hdr_el(c, t), dev_err, ok).x);
+        for (int t = lane; t < P; t += 64) lv = fmax(lv, rec_poll(rs, SLOT_HDR + c * P + t, dev_err, ok).x);
         lv = wave_max_f64(lv);
         int li = 0x7fffffff;
         if (lv >= 0.0)
           for (int t = lane; t < P; t += 64)
-            if (rec_poll(rs, hdr_el(c, t), dev_err, ok).x == lv) {
+            if (rec_poll(rs, SLOT_HDR + c * P + t, dev_err, ok).x == lv) {
               li = t;
               break;
             }
@@ -362,7 +357,7 @@ __global__ __launch_bounds__(SNT) void panel_kernel(int N, T *A, long lda, int j
         if (li != 0x7fffffff) {
           ww = li;
           vw = lv;
-          pw = (long)rec_poll(rs, hdr_el(c, li), dev_err, ok).y;
+          pw = (long)rec_poll(rs, SLOT_HDR + c * P + li, dev_err, ok).y;
         }
       }
       if (ww < 0) {  // no comparable candidate (a column of NaNs): keep the diagonal row, report it
@@ -373,8 +368,8 @@ __global__ __launch_bounds__(SNT) void panel_kernel(int N, T *A, long lda, int j
       // the winner's row and the diagonal row, both loads in flight together
       cplx dr = cmk(0, 0), pr;
       {
-        const int ed = col_ok ? base + P * rstr + lane : -1;
-        const int er = (col_ok && ww >= 0) ? base + ww * rstr + 1 + lane : -1;
+        const int ed = col_ok ? base + P * rec + lane : -1;
+        const int er = (col_ok && ww >= 0) ? base + ww * rec + 1 + lane : -1;
         bm_v4i vd, vr;
         if (ed >= 0) vd = rec_load(rs, ed);
         if (er >= 0) vr = rec_load(rs, er);
@@ -462,8 +457,8 @@ __global__ __launch_bounds__(SNT) void panel_kernel(int N, T *A, long lda, int j
         const int base1 = (c + 1) * cstride;
         const long ld = gc + 1 - r0;
         const bool has_d = (ld >= 0 && ld < nv);
-        if (col_ok) rec_store(rs, base1 + g * rstr + 1 + lane, (lr >= 0) ? rec_row(lr) : cmk(0, 0));
-        if (col_ok && has_d) rec_store(rs, base1 + P * rstr + lane, rec_row((int)ld));
+        if (col_ok) rec_store(rs, base1 + g * rec + 1 + lane, (lr >= 0) ? rec_row(lr) : cmk(0, 0));
+        if (col_ok && has_d) rec_store(rs, base1 + P * rec + lane, rec_row((int)ld));
       }
       // now LDS: the interchanged rows; column c + 2 with pivot c applied, kept in
       // registers for the next step (in LDS it stays one pivot behind, like the
@@ -1112,9 +1107,10 @@ static int getrf_run_batch(hipStream_t s, int n, int count, T *const *A, int64_t
   const int fit = lu_batch_fit(n, count, ncu);
   if (fit < 1) return BM_E_ARG;
   if (fit < count) {
-    for (int b = 0; b < count; b += fit)
-      if (int rc = getrf_run_batch(s, n, (count - b < fit) ? count - b : fit, A + b, lda, ipiv + b, dev_err + b, ws + b))
-        return rc;
+    for (int b = 0; b < count; b += fit) {
+      const int part = (count - b < fit) ? count - b : fit;
+      if (int rc = getrf_run_batch(s, n, part, A + b, lda, ipiv + b, dev_err + b, ws + b)) return rc;
+    }
     return BM_OK;
   }
   for (int b = 0; b < count; ++b)  // per problem: flags and the first panel's exchange words

@@ -177,12 +177,6 @@ __device__ inline void tile_mv8(const st_v2 (&t)[16], const double (&bz)[16], cp
   o1.y += sign * (a[3] + b[1]);
 }
 
-// candidate order: larger value wins, then the smaller row
-__device__ inline bool better(double v, long g, double bv, long bg) {
-  return (v > bv) || (v == bv && g >= 0 && (bg < 0 || g < bg));
-}
-
-
 // ---------------------------------------------------------------------------
 // problem handle
 // ---------------------------------------------------------------------------

@@ -12,16 +12,18 @@
 // Rows are not moved.  A row keeps its register slot (slot r holds row j + r of the
 // panel as it came); an extra wavefront of each workgroup, the clerk, follows the
 // interchanges in LDS, which gives ties their order (smallest position first) and the
-// rows their places at the end, keeps the rows of U and publishes the pivots.  A row that has been a pivot is final right of the diagonal: its entries
-// move to LDS (s_u) and the row is marked (gone[]) for the search; the update runs over
-// all rows with no test, and what it leaves in such a row is not used.
+// rows their places at the end, keeps the rows of U and publishes the pivots.  A row
+// that has been a pivot is final right of the diagonal: its entries move to LDS (s_u)
+// and the row is marked (gone[]) for the search; the update runs over all rows with no
+// test, and what it leaves in such a row is not used.
 //
 // What bounds a column is the length of its chain of dependent instructions, each a
 // few cycles, so the search compares the high words of |Re| + |Im| only (an integer
-// maximum).  Where two rows share the largest high word, or the largest is zero,
-// denormal, infinite or NaN, the column takes the exact search instead.  Measured per
-// column: 0.65 us at 64 rows to 1.25 us at 2048 and 1.7 at 2688 (2.05 to 2.3 us with an exchange of
-// candidates between workgroups of 64 or 128 rows), a hand-off between workgroups 0.5 to 1 us.
+// maximum).  Where two rows share the largest high word, or the largest is zero (values
+// below 2^-1042), infinite or NaN, the column takes the exact search instead.  Measured
+// per column: 0.65 us at 64 rows to 1.25 us at 2048 and 1.7 at 2688 (2.05 to 2.3 us with
+// an exchange of candidates between workgroups of 64 or 128 rows), a hand-off between
+// workgroups 0.5 to 1 us.
 //
 // Exchange words, each 16 bytes, written once with agent scope over the empty
 // pattern and polled by the readers:
@@ -35,7 +37,8 @@ __device__ inline void spn_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_b
 // lane I of each row of 16 lanes, in every lane of the row
 template <int I>
 __device__ inline double row_bcast_f64(double v) {
-  return __longlong_as_double(__builtin_amdgcn_update_dpp(0l, (long)__double_as_longlong(v), 0x150 + I, 0xf, 0xf, true));
+  const long w = (long)__double_as_longlong(v);
+  return __longlong_as_double(__builtin_amdgcn_update_dpp(0l, w, 0x150 + I, 0xf, 0xf, true));
 }
 // (every lane of these patterns has a source, so the move folds into the maximum)
 template <int CTRL>

@@ -60,7 +60,7 @@ int bm_launch_gather(hipStream_t s, int nf, int nrhs, const int32_t *perm, const
 // stage 1: workgroup (256-row block, k split) -> partial sums; thread = row, the
 //          k-slice of B staged in LDS and broadcast to the 256 rows; the A loads of
 //          eight k values are issued together (unconditionally: rows past m read
-//          row 0), and the accumulators are sized for the right-hand-side count
+//          row 0); up to GV_NR right-hand sides (more: skinny_partial_kernel)
 // stage 2: partials summed in split order and subtracted from C
 // The k split aims at GV_WG workgroups with at least GV_KC k values each, so that
 // A (read once) dominates the traffic and the partials stay small.
@@ -68,22 +68,22 @@ int bm_launch_gather(hipStream_t s, int nf, int nrhs, const int32_t *perm, const
 #define GV_ROWS 256
 #define GV_KC 32
 #define GV_UN 8
+#define GV_NR 8
 #define GV_WG 768  // enough workgroups (three per CU) to keep HBM busy: 256 reached a third of it
-template <int NRM>
 __global__ __launch_bounds__(256) void gemv_partial_kernel(int m, int k, int nr, int kchunk, const cplx *A, long lda,
                                                            const cplx *B, long ldb, cplx *part) {
-  __shared__ cplx Bs[GV_KC][NRM];
+  __shared__ cplx Bs[GV_KC][GV_NR];
   const int i = blockIdx.x * GV_ROWS + threadIdx.x;
   const int ia = (i < m) ? i : 0;
   const int ks = blockIdx.y;
   const int k0 = ks * kchunk, k1 = (k0 + kchunk < k) ? k0 + kchunk : k;
-  cplx acc[NRM];
+  cplx acc[GV_NR];
 #pragma unroll
-  for (int r = 0; r < NRM; ++r) acc[r] = cmk(0, 0);
+  for (int r = 0; r < GV_NR; ++r) acc[r] = cmk(0, 0);
   for (int kb = k0; kb < k1; kb += GV_KC) {
     const int kn = (k1 - kb < GV_KC) ? k1 - kb : GV_KC;
     __syncthreads();
-    for (int idx = threadIdx.x; idx < GV_KC * NRM; idx += 256) {
+    for (int idx = threadIdx.x; idx < GV_KC * GV_NR; idx += 256) {
       const int kk = idx % GV_KC, r = idx / GV_KC;
       Bs[kk][r] = (kk < kn && r < nr) ? B[(kb + kk) + (long)r * ldb] : cmk(0, 0);
     }
@@ -97,14 +97,14 @@ __global__ __launch_bounds__(256) void gemv_partial_kernel(int m, int k, int nr,
         // Bs rows past kn are zero, so the clamped loads add nothing
         const cplx av = cmk(a[u].x, a[u].y);
 #pragma unroll
-        for (int r = 0; r < NRM; ++r) acc[r] = cadd(acc[r], cmul(av, Bs[u0 + u][r]));
+        for (int r = 0; r < GV_NR; ++r) acc[r] = cadd(acc[r], cmul(av, Bs[u0 + u][r]));
       }
     }
   }
   if (i < m) {
     cplx *pp = part + (size_t)ks * m * nr;
 #pragma unroll
-    for (int r = 0; r < NRM; ++r)
+    for (int r = 0; r < GV_NR; ++r)
       if (r < nr) pp[i + (size_t)r * m] = acc[r];
   }
 }
@@ -112,42 +112,37 @@ __global__ __launch_bounds__(256) void gemv_partial_kernel(int m, int k, int nr,
 // Stage 1 for more than eight right-hand sides, on the FP64 matrix cores (the FP64
 // vector form above reads every element of B from LDS once per row and right-hand
 // side: 530 us for the 4096 x 8192 block with 32 of them, 1 TB/s of A).  A wavefront
-// owns 16 H rows and all right-hand sides, in groups of eight whose 16 real columns
+// owns 16 rows and all right-hand sides, in groups of eight whose 16 real columns
 // [Re | Im] are the matrix instruction's columns (tile_mv8); lane (fi, fq) loads
 // A(row fi, k = fq) of each 4-deep step straight from memory, and the workgroup's
 // slice of B goes through LDS in operand order.  The steps of a slice of SK_KC are
-// loaded together, one slice ahead.  Solve with 32 right-hand sides, N = 4096: 1068 us
-// with H = 2 and slices of 16, 994 us with H = 1 and slices of 32 (more wavefronts per
-// SIMD; 1028 us with slices of 16 and 1024 workgroups).
+// loaded together, one slice ahead.  Solve with 32 right-hand sides, N = 4096: 994 us;
+// 1068 us with 32 rows per wavefront and slices of 16 (fewer wavefronts per SIMD),
+// 1028 us with 16 rows, slices of 16 and 1024 workgroups.
 #define SK_ROWS 64  // rows per workgroup
 #define SK_KC 32
 #define SK_WG 512
-template <int NG, int H>
+template <int NG>
 __global__ __launch_bounds__(256) void skinny_partial_kernel(int m, int k, int nr, int kchunk, const cplx *A, long lda,
                                                              const cplx *B, long ldb, cplx *part) {
   constexpr int ST = SK_KC / 4;
   __shared__ double Bs[2][ST * NG * 64];  // [step][group][lane]: the operand of the lane
   const int tid = threadIdx.x, lane = tid & 63, fi = lane & 15, fq = lane >> 4;
-  const int r0 = (blockIdx.x * 4 + (tid >> 6)) * 16 * H;
+  const int r0 = blockIdx.x * SK_ROWS + (tid >> 6) * 16;
   const int ks = blockIdx.y;
   const int k0 = ks * kchunk, k1 = (k0 + kchunk < k) ? k0 + kchunk : k;
-  tv_dbl4 c1[H][NG], c2[H][NG];
+  tv_dbl4 c1[NG], c2[NG];
 #pragma unroll
-  for (int h = 0; h < H; ++h)
-#pragma unroll
-    for (int g = 0; g < NG; ++g) c1[h][g] = c2[h][g] = (tv_dbl4){0, 0, 0, 0};
+  for (int g = 0; g < NG; ++g) c1[g] = c2[g] = (tv_dbl4){0, 0, 0, 0};
   // rows past m and columns past the slice read a valid address; the rows are not
   // stored and the columns meet zero operands
-  long row[H];
-#pragma unroll
-  for (int h = 0; h < H; ++h) row[h] = (r0 + 16 * h + fi < m) ? r0 + 16 * h + fi : 0;
-  st_v2 av[H][ST];
+  const long row = (r0 + fi < m) ? r0 + fi : 0;
+  st_v2 av[ST];
   auto load_a = [&](int kb) __attribute__((always_inline)) {
 #pragma unroll
     for (int s = 0; s < ST; ++s) {
       const int kk = kb + 4 * s + fq;
-#pragma unroll
-      for (int h = 0; h < H; ++h) av[h][s] = st_ld(A, row[h] + (long)(kk < k1 ? kk : k0) * lda);
+      av[s] = st_ld(A, row + (long)(kk < k1 ? kk : k0) * lda);
     }
   };
   // one value of B per thread and NG * ST * 64 / 256 of them
@@ -169,11 +164,9 @@ __global__ __launch_bounds__(256) void skinny_partial_kernel(int m, int k, int n
   for (int kb = k0; kb < k1; kb += SK_KC, buf ^= 1) {
 #pragma unroll
     for (int q = 0; q < BV; ++q) Bs[buf][tid + 256 * q] = bv[q];
-    st_v2 at[H][ST];
+    st_v2 at[ST];
 #pragma unroll
-    for (int h = 0; h < H; ++h)
-#pragma unroll
-      for (int s = 0; s < ST; ++s) at[h][s] = av[h][s];
+    for (int s = 0; s < ST; ++s) at[s] = av[s];
     if (kb + SK_KC < k1) {
       load_b(kb + SK_KC);
       load_a(kb + SK_KC);
@@ -184,24 +177,18 @@ __global__ __launch_bounds__(256) void skinny_partial_kernel(int m, int k, int n
 #pragma unroll
       for (int g = 0; g < NG; ++g) {
         const double b = Bs[buf][(s * NG + g) * 64 + lane];
-#pragma unroll
-        for (int h = 0; h < H; ++h) {
-          c1[h][g] = __builtin_amdgcn_mfma_f64_16x16x4f64(b, at[h][s].x, c1[h][g], 0, 0, 0);
-          c2[h][g] = __builtin_amdgcn_mfma_f64_16x16x4f64(b, at[h][s].y, c2[h][g], 0, 0, 0);
-        }
+        c1[g] = __builtin_amdgcn_mfma_f64_16x16x4f64(b, at[s].x, c1[g], 0, 0, 0);
+        c2[g] = __builtin_amdgcn_mfma_f64_16x16x4f64(b, at[s].y, c2[g], 0, 0, 0);
       }
   }
-  cplx *pp = part + (size_t)ks * m * nr;
+  const int i = r0 + fi;
+  if (i < m) {
+    cplx *pp = part + (size_t)ks * m * nr;
 #pragma unroll
-  for (int h = 0; h < H; ++h) {
-    const int i = r0 + 16 * h + fi;
-    if (i < m) {
-#pragma unroll
-      for (int g = 0; g < NG; ++g) {
-        const tv_dbl4 a = c1[h][g], b = c2[h][g];
-        if (8 * g + fq < nr) pp[i + (size_t)(8 * g + fq) * m] = cmk(a[0] - b[2], a[2] + b[0]);
-        if (8 * g + 4 + fq < nr) pp[i + (size_t)(8 * g + 4 + fq) * m] = cmk(a[1] - b[3], a[3] + b[1]);
-      }
+    for (int g = 0; g < NG; ++g) {
+      const tv_dbl4 a = c1[g], b = c2[g];
+      if (8 * g + fq < nr) pp[i + (size_t)(8 * g + fq) * m] = cmk(a[0] - b[2], a[2] + b[0]);
+      if (8 * g + 4 + fq < nr) pp[i + (size_t)(8 * g + 4 + fq) * m] = cmk(a[1] - b[3], a[3] + b[1]);
     }
   }
 }
@@ -241,10 +228,9 @@ int bm_launch_gemv_sub(hipStream_t s, int m, int k, int nr, const cplx *A, int64
   if (nr > BM_MAX_NRHS) return BM_E_ARG;
   int ns, kchunk;
   gemv_split(m, k, &ns, &kchunk);
-  if (nr <= 8) {
+  if (nr <= GV_NR) {
     const dim3 grid((m + GV_ROWS - 1) / GV_ROWS, ns);
-    hipLaunchKernelGGL(gemv_partial_kernel<8>, grid, dim3(256), 0, s, m, k, nr, kchunk, A, (long)lda, B, (long)ldb,
-                       work);
+    hipLaunchKernelGGL(gemv_partial_kernel, grid, dim3(256), 0, s, m, k, nr, kchunk, A, (long)lda, B, (long)ldb, work);
   } else {
     // the matrix-core form: fewer, deeper slices (its partials are up to four times as
     // wide), never more than the workspace holds
@@ -255,10 +241,10 @@ int bm_launch_gemv_sub(hipStream_t s, int m, int k, int nr, const cplx *A, int64
     ns = (k + kchunk - 1) / kchunk;
     const dim3 grid(rb, ns);
     if (nr <= 16)
-      hipLaunchKernelGGL((skinny_partial_kernel<2, SK_ROWS / 64>), grid, dim3(256), 0, s, m, k, nr, kchunk, A, (long)lda, B, (long)ldb,
+      hipLaunchKernelGGL(skinny_partial_kernel<2>, grid, dim3(256), 0, s, m, k, nr, kchunk, A, (long)lda, B, (long)ldb,
                          work);
     else
-      hipLaunchKernelGGL((skinny_partial_kernel<4, SK_ROWS / 64>), grid, dim3(256), 0, s, m, k, nr, kchunk, A, (long)lda, B, (long)ldb,
+      hipLaunchKernelGGL(skinny_partial_kernel<4>, grid, dim3(256), 0, s, m, k, nr, kchunk, A, (long)lda, B, (long)ldb,
                          work);
   }
   BM_HIP_TRY(hipGetLastError());
