@@ -249,8 +249,8 @@ int bm_set_quadrature(bm_problem *p, int32_t quadrature);
  * the same pivoting rule; the segmented product sums k in slices for its first
  * columns, so the two agree to rounding, not bitwise.  Available for the mixed
  * form with N <= 4096 in FP64 precision (the default there; the mixed-precision
- * factorisation always forms U33 first).  Errors: BM_E_ARG (on = 1 where it is
- * not available). */
+ * factorisation always forms U33 first, and so does one whose stream is being
+ * captured into a HIP graph).  Errors: BM_E_ARG (on = 1 where it is not available). */
 int bm_set_lu_overlap(bm_problem *p, int32_t on);
 
 /* Host pointers: *enabled the setting of bm_set_lu_overlap; *segments the

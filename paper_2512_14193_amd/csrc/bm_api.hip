@@ -314,6 +314,17 @@ static int schur_product(bm_problem *p) {
   return bm_launch_zgemm(p->stream, n, n, 2 * n, cmk(-1.0, 0.0), p->bot, n, p->top, 2 * n, cmk(0.0, 0.0), p->lu, n);
 }
 
+// Whether s is being captured into a graph (the default stream cannot be).
+static bool is_captured(hipStream_t s) {
+  if (s == nullptr) return false;
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return st != hipStreamCaptureStatusNone;
+}
+
 int bm_block_lu(bm_problem *p, int32_t *info) {
   if (!p) return BM_E_ARG;
   if (p->state < BM_ST_ASSEMBLED) return BM_E_STATE;
@@ -326,7 +337,10 @@ int bm_block_lu(bm_problem *p, int32_t *info) {
   // a refinement flag left by a solve with the previous factors does not apply
   if (p->form == BM_MIXED)
     if (int rc0 = bm_launch_ir_reset(p->stream, p->ir_norm + 2 * BM_MAX_NRHS, p->dev_err + 3, 0)) return rc0;
-  if (p->form == BM_MIXED && p->prec == BM_PREC_FP64 && p->pipeline) {
+  // Under capture U33 is formed first, with one stream beside the problem's.  The overlapped
+  // form's side streams wait for each other as well, and a capture in which streams had
+  // joined through each other ended the process.
+  if (p->form == BM_MIXED && p->prec == BM_PREC_FP64 && p->pipeline && !is_captured(p->stream)) {
     if (int rc0 = bm_getrf_pipe_create(p->gws)) return rc0;
     // Theorem thm:LU: U33 = -M31 M13 - M32 M23 = -[M31 M32] [M13; M23], formed in
     // column segments beside the factorisation of the columns already formed
