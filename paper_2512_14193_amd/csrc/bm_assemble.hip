@@ -27,7 +27,7 @@
 static int bm_domain(const bm_problem *p) {
   const bm_phys &ph = p->phys;
   if (ph.k0.y >= -0.5 * ph.k0.x && ph.k1.y >= -0.5 * ph.k1.x) return BM_DOM_SECTOR;
-  return (p->n <= BM_WIDE_SUM_MAX_N) ? BM_DOM_WIDE_SUM : BM_DOM_WIDE;
+  return (p->n <= BM_WIDE_LOCAL_MAX_N) ? BM_DOM_WIDE_LOCAL : BM_DOM_WIDE;
 }
 
 // The Hankel tables of the problem's wavenumbers (complex ones, and the wide domain),
@@ -35,7 +35,7 @@ static int bm_domain(const bm_problem *p) {
 int bm_launch_hankel_rays(const bm_problem *p) {
   const bm_phys &ph = p->phys;
   const int dom = bm_domain(p);
-  if (dom == BM_DOM_WIDE_SUM || (dom == BM_DOM_SECTOR && ph.k0.y == 0.0 && ph.k1.y == 0.0)) return BM_OK;
+  if (dom == BM_DOM_WIDE_LOCAL || (dom == BM_DOM_SECTOR && ph.k0.y == 0.0 && ph.k1.y == 0.0)) return BM_OK;
   hipLaunchKernelGGL(hankel_ray_kernel, dim3(2), dim3(HK_RAY_NT), 0, p->stream, ph.k0, ph.k1,
                      (hk_ray *)(p->wts + 4 * (size_t)p->n));
   BM_HIP_TRY(hipGetLastError());
@@ -184,16 +184,22 @@ struct pair_k {
 };
 
 // The Hankel values at k r (real wavenumbers outside the wide domain need no table).
-template <int DOM>
-__device__ inline bm_hk4 hankel_at(cplx k, const hk_ray *ray, double r, double rinv, bool *bad) {
-  if (DOM == BM_DOM_WIDE_SUM) return bm_hankel01_wide(cscale(k, r), bad);
-  if (DOM == BM_DOM_SECTOR && k.y == 0.0) return bm_hankel01_real(k.x * r);
-  return bm_hankel01_ray<DOM == BM_DOM_WIDE>(ray, r, rinv, bad);
+// W: the tables, const hk_ray * or, for BM_DOM_WIDE_LOCAL, the workgroup's const hk_wave *
+template <int DOM, class W>
+__device__ inline bm_hk4 hankel_at(cplx k, W ray, double r, double rinv, bool *bad) {
+  if constexpr (DOM == BM_DOM_SECTOR) {
+    return (k.y == 0.0) ? bm_hankel01_real(k.x * r) : bm_hankel01_ray(ray, r, rinv);
+  } else if constexpr (DOM == BM_DOM_WIDE) {
+    typedef const __attribute__((address_space(4))) hk_ray *ray_ptr;  // (constant: scalar loads)
+    return bm_hankel01_wide(&((ray_ptr)ray)->w, r, rinv, bad);
+  } else {
+    return bm_hankel01_wide(ray, r, rinv, bad);
+  }
 }
 
-template <int DOM>
-__device__ inline pair_k pair_scalars(cplx k, const hk_ray *ray, double r, double rinv, double R, double L, double h,
-                                      double a, double b, bool want_nu, bool *bad) {
+template <int DOM, class W>
+__device__ inline pair_k pair_scalars(cplx k, W ray, double r, double rinv, double R, double L, double h, double a,
+                                      double b, bool want_nu, bool *bad) {
   const bm_hk4 hk = hankel_at<DOM>(k, ray, r, rinv, bad);
   pair_k o;
   // S: K = (i/4) H0, K1 = -J0/(4 pi)
@@ -338,6 +344,14 @@ __global__ __launch_bounds__(256) void assemble_kernel(asm_args A) {
   const int I = (int)(Lt - (long)J * (J + 1) / 2);
 
   __shared__ cplx mirror[4][ASM_TB][ASM_TB + 1];
+  __shared__ hk_wave wave[DOM == BM_DOM_WIDE_LOCAL ? 2 : 1];
+  if constexpr (DOM == BM_DOM_WIDE_LOCAL) {
+    // a wavefront for the series of each wavenumber, one for the rest of its tables
+    const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
+    const int item = (w < 2) ? ((l < HK_NS) ? l : -1) : ((l == 0) ? HK_NS : -1);
+    if (item >= 0) hk_wave_item((w & 1) ? A.ph.k1 : A.ph.k0, item, &wave[w & 1]);
+    __syncthreads();
+  }
 
   const int N = A.N;
   const int li = threadIdx.x % ASM_TB, lj = threadIdx.x / ASM_TB;
@@ -351,8 +365,14 @@ __global__ __launch_bounds__(256) void assemble_kernel(asm_args A) {
       const pair_geo g = pair_geometry(A, i, j);
       const double si = g.si, sj = g.sj, ndi = g.ndi, ndj = g.ndj, kap = g.kap;
       bool bad = false;
-      const pair_k p0 = pair_scalars<DOM>(ph.k0, A.ray, g.r, g.rinv, g.R, g.L, A.h, g.a, g.b, true, &bad);
-      const pair_k p1 = pair_scalars<DOM>(ph.k1, A.ray + 1, g.r, g.rinv, g.R, g.L, A.h, g.a, g.b, false, &bad);
+      pair_k p0, p1;
+      if constexpr (DOM == BM_DOM_WIDE_LOCAL) {
+        p0 = pair_scalars<DOM>(ph.k0, &wave[0], g.r, g.rinv, g.R, g.L, A.h, g.a, g.b, true, &bad);
+        p1 = pair_scalars<DOM>(ph.k1, &wave[1], g.r, g.rinv, g.R, g.L, A.h, g.a, g.b, false, &bad);
+      } else {
+        p0 = pair_scalars<DOM>(ph.k0, A.ray, g.r, g.rinv, g.R, g.L, A.h, g.a, g.b, true, &bad);
+        p1 = pair_scalars<DOM>(ph.k1, A.ray + 1, g.r, g.rinv, g.R, g.L, A.h, g.a, g.b, false, &bad);
+      }
       if (DOM != BM_DOM_SECTOR && bad) atomicOr(A.dom_err, 1);
       // k0 operators at (i,j) and (j,i)
       const cplx S0ij = cscale(p0.sig, sj), S0ji = cscale(p0.sig, si);
@@ -423,9 +443,9 @@ int bm_launch_assemble(bm_problem *p, const bm_geometry *g) {
   typedef void (*assemble_fn)(asm_args);
   static const assemble_fn fns[2][3] = {  // by formulation and BM_DOM_*
       {assemble_kernel<BM_MIXED, BM_DOM_SECTOR>, assemble_kernel<BM_MIXED, BM_DOM_WIDE>,
-       assemble_kernel<BM_MIXED, BM_DOM_WIDE_SUM>},
+       assemble_kernel<BM_MIXED, BM_DOM_WIDE_LOCAL>},
       {assemble_kernel<BM_ORDINARY, BM_DOM_SECTOR>, assemble_kernel<BM_ORDINARY, BM_DOM_WIDE>,
-       assemble_kernel<BM_ORDINARY, BM_DOM_WIDE_SUM>}};
+       assemble_kernel<BM_ORDINARY, BM_DOM_WIDE_LOCAL>}};
   hipLaunchKernelGGL(fns[p->form == BM_MIXED ? 0 : 1][bm_domain(p)], grid, dim3(256), 0, p->stream, A);
   BM_HIP_TRY(hipGetLastError());
   return BM_OK;

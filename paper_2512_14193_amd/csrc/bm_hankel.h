@@ -33,10 +33,13 @@
 // (the last term is below 1e-26 of the largest); in the lower half plane J and Y grow
 // like H^(1), so the series loses at most a factor e^{|z| - |Im z|} <= 30 to
 // cancellation.  Larger |z| is outside the supported domain: the caller flags it.
-// Up to BM_WIDE_SUM_MAX_N nodes each pair sums its own terms: the tables' kernel and
-// their loads, 18 and 9 us, are then more than they save.  Assembly by pairs and by
-// tables: N = 128 22 and 48 us, 512 34 and 54, 1024 66 and 69, 1100 72 and 71,
-// 1400 105 and 84, 2048 198 and 131 (both formulations alike).
+// Up to BM_WIDE_LOCAL_MAX_N nodes each workgroup of the assembly makes the tables of the
+// series for itself, in LDS, about 2 us of each: the kernel that makes them once takes
+// 11 us (17 before the factorials became compile-time constants), and its tables arrive
+// cold.  Assembly with tables made by each workgroup and made
+// once (both formulations alike): N = 128 25 and 41 us, 512 30 and 46, 1024 51 and 62,
+// 1200 62 and 69, 1400 74 and 78, 1600 88 and 88, 2048 134 and 125, 4000 478 and 390 (LDS
+// reads, which the scalar loads spare).
 #pragma once
 
 #include "bm_internal.h"
@@ -138,126 +141,97 @@ __device__ inline bm_hk4 bm_hankel01_real(double x) {
 
 // How the Hankel values of an assembly are evaluated
 enum {
-  BM_DOM_SECTOR,    // wavenumbers in the sector
-  BM_DOM_WIDE,      // the wide domain, by tables
-  BM_DOM_WIDE_SUM,  // the wide domain, each pair its own sum
+  BM_DOM_SECTOR,      // wavenumbers in the sector
+  BM_DOM_WIDE,        // the wide domain, tables made once
+  BM_DOM_WIDE_LOCAL,  // the wide domain, tables made by each workgroup
 };
-#define BM_WIDE_SUM_MAX_N 1024
+#define BM_WIDE_LOCAL_MAX_N 1200
 #define BM_WIDE_ZMAX 6.0  // largest |z| of the wide domain
 
-// The power series at complex z (NT terms)
-template <int NT>
-__device__ inline void bm_hankel_sum(cplx z, bm_hk4 &o) {
-  const cplx mw = cscale(cmul(z, z), -0.25);  // -z^2/4
-  cplx t0 = cmk(1.0, 0.0), t1 = cmk(1.0, 0.0);
-  cplx sj0 = cmk(0, 0), sj1 = cmk(0, 0), sy0 = cmk(0, 0), sy1 = cmk(0, 0);
-  double hk = 0.0, hk1 = 1.0;  // harmonic numbers H_k, H_{k+1}
-#pragma unroll
-  for (int k = 0; k < NT; ++k) {
-    sj0 = cadd(sj0, t0);
-    sj1 = cadd(sj1, t1);
-    sy0 = cadd(sy0, cscale(t0, hk));
-    sy1 = cadd(sy1, cscale(t1, hk + hk1));
-    t0 = cscale(cmul(t0, mw), 1.0 / ((k + 1.0) * (k + 1.0)));
-    t1 = cscale(cmul(t1, mw), 1.0 / ((k + 1.0) * (k + 2.0)));
-    hk = hk1;
-    hk1 += 1.0 / (k + 2.0);
-  }
-  const cplx zh = cscale(z, 0.5);
-  const cplx J0 = sj0, J1 = cmul(zh, sj1);
-  cplx L = clog_d(zh);
-  L.x += BM_EULER;
-  const cplx Y0 = cscale(csub(cmul(L, J0), sy0), 2.0 / BM_PI);
-  const cplx Y1 = cadd(cadd(cscale(crecip(z), -2.0 / BM_PI), cscale(cmul(L, J1), 2.0 / BM_PI)),
-                       cscale(cmul(zh, sy1), -1.0 / BM_PI));
-  o.j0 = J0;
-  o.j1 = J1;
-  o.h0 = cmk(J0.x - Y0.y, J0.y + Y0.x);
-  o.h1 = cmk(J1.x - Y1.y, J1.y + Y1.x);
-}
-
-// The wide domain without tables; *bad is set when |z| >= BM_WIDE_ZMAX.
-__device__ inline bm_hk4 bm_hankel01_wide(cplx z, bool *bad) {
-  bm_hk4 o;
-  const double az2 = cabs2(z);
-  if (az2 < 9.0) {
-    bm_hankel_sum<18>(z, o);
-  } else {
-    if (!(az2 < BM_WIDE_ZMAX * BM_WIDE_ZMAX)) *bad = true;
-    bm_hankel_sum<26>(z, o);
-  }
-  return o;
-}
-
-// Tables of one wavenumber k = ak e^{i th} (hankel_ray_kernel); every lane reads the
-// same entries, so they come through the scalar cache.
+// Tables of one wavenumber k = ak e^{i th}; every lane reads the same entries, so those
+// made once (hankel_ray_kernel) come through the scalar cache.
 #define HK_NS 26          // series terms (18 for |z| < 3)
 #define HK_NC 28          // Chebyshev coefficients (those of degree 24 and beyond are below 1e-16)
-struct hk_ray {
-  double ak, th;        // |k|, arg k
-  cplx k, sq1, sq2, ik;  // k, sqrt(2/pi) e^{-i th/2 -+ i pi/4}, 1/k
-  double scale, pad[5];  // the power of two P with P <= |k| < 2 P
+struct hk_wave {
+  double ak, th;   // |k|, arg k
+  cplx k, ik;      // k, 1/k
+  double scale, pad;    // the power of two P with P <= |k| < 2 P
   double ser[HK_NS][8];  // J0, J1 / (z/2), and the harmonic sums of Y0, Y1: coefficients in (P r)^2
+};
+struct hk_ray {
+  hk_wave w;
+  cplx sq1, sq2;          // sqrt(2/pi) e^{-i th/2 -+ i pi/4}
   double cheb[HK_NC][8];  // F_0 - 1, F_1 - 1 of H^(1) and of H^(2), in u = 6/|z| - 1
 };
 #define HK_RAY_DOUBLES (sizeof(hk_ray) / sizeof(double))
 
-template <bool WIDE>
-__device__ inline bm_hk4 bm_hankel01_ray(const hk_ray *T_, double r, double rinv, bool *bad) {
+// The power series (NT terms) at r, az = |k| r.  W: the hk_wave, in constant memory or LDS
+template <int NT, class W>
+__device__ inline bm_hk4 hk_series_at(W T, double r, double rinv, double az) {
+  bm_hk4 o;
+  const double xr = T->scale * r, x = xr * xr;
+  double s[8];
+#pragma unroll
+  for (int q = 0; q < 8; ++q) s[q] = T->ser[NT - 1][q];
+#pragma unroll 2
+  for (int m = NT - 2; m >= 0; --m)
+#pragma unroll
+    for (int q = 0; q < 8; ++q) s[q] = fma(s[q], x, T->ser[m][q]);
+  const cplx zh = cmk(0.5 * T->k.x * r, 0.5 * T->k.y * r), zi = cmk(T->ik.x * rinv, T->ik.y * rinv);
+  const cplx J0 = cmk(s[0], s[1]), J1 = cmul(zh, cmk(s[2], s[3]));
+  const cplx L = cmk(log(0.5 * az) + BM_EULER, T->th);
+  const cplx Y0 = cscale(csub(cmul(L, J0), cmk(s[4], s[5])), 2.0 / BM_PI);
+  const cplx Y1 = cadd(cadd(cscale(zi, -2.0 / BM_PI), cscale(cmul(L, J1), 2.0 / BM_PI)),
+                       cscale(cmul(zh, cmk(s[6], s[7])), -1.0 / BM_PI));
+  o.j0 = J0;
+  o.j1 = J1;
+  o.h0 = cmk(J0.x - Y0.y, J0.y + Y0.x);
+  o.h1 = cmk(J1.x - Y1.y, J1.y + Y1.x);
+  return o;
+}
+
+// The wide domain; *bad is set when |z| >= BM_WIDE_ZMAX.
+template <class W>
+__device__ inline bm_hk4 bm_hankel01_wide(W T, double r, double rinv, bool *bad) {
+  const double az = T->ak * r;
+  if (!(az < BM_WIDE_ZMAX)) *bad = true;
+  return hk_series_at<HK_NS>(T, r, rinv, az);
+}
+
+// The sector, from the tables made once
+__device__ inline bm_hk4 bm_hankel01_ray(const hk_ray *T_, double r, double rinv) {
   typedef const __attribute__((address_space(4))) hk_ray *ray_ptr;  // (constant: scalar loads)
   const ray_ptr T = (ray_ptr)T_;
+  const double az = T->w.ak * r;
+  if (az < 3.0) return hk_series_at<18>(&T->w, r, rinv, az);
   bm_hk4 o;
-  const double az = T->ak * r;
-  if (WIDE || az < 3.0) {
-    if (WIDE && !(az < BM_WIDE_ZMAX)) *bad = true;
-    constexpr int NT = WIDE ? HK_NS : 18;
-    const double xr = T->scale * r, x = xr * xr;
-    double s[8];
+  const double t = 1.0 / az, u = 6.0 * t - 1.0, u2 = 2.0 * u;
+  double b1[8], b2[8];
 #pragma unroll
-    for (int q = 0; q < 8; ++q) s[q] = T->ser[NT - 1][q];
-#pragma unroll 2
-    for (int m = NT - 2; m >= 0; --m)
-#pragma unroll
-      for (int q = 0; q < 8; ++q) s[q] = fma(s[q], x, T->ser[m][q]);
-    const cplx zh = cmk(0.5 * T->k.x * r, 0.5 * T->k.y * r), zi = cmk(T->ik.x * rinv, T->ik.y * rinv);
-    const cplx J0 = cmk(s[0], s[1]), J1 = cmul(zh, cmk(s[2], s[3]));
-    const cplx L = cmk(log(0.5 * az) + BM_EULER, T->th);
-    const cplx Y0 = cscale(csub(cmul(L, J0), cmk(s[4], s[5])), 2.0 / BM_PI);
-    const cplx Y1 = cadd(cadd(cscale(zi, -2.0 / BM_PI), cscale(cmul(L, J1), 2.0 / BM_PI)),
-                         cscale(cmul(zh, cmk(s[6], s[7])), -1.0 / BM_PI));
-    o.j0 = J0;
-    o.j1 = J1;
-    o.h0 = cmk(J0.x - Y0.y, J0.y + Y0.x);
-    o.h1 = cmk(J1.x - Y1.y, J1.y + Y1.x);
-  } else {
-    const double t = 1.0 / az, u = 6.0 * t - 1.0, u2 = 2.0 * u;
-    double b1[8], b2[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) b1[q] = b2[q] = 0.0;
+  for (int q = 0; q < 8; ++q) b1[q] = b2[q] = 0.0;
 #pragma unroll 3
-    for (int j = HK_NC - 1; j >= 1; --j)
+  for (int j = HK_NC - 1; j >= 1; --j)
 #pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        const double bn = fma(u2, b1[q], T->cheb[j][q] - b2[q]);
-        b2[q] = b1[q];
-        b1[q] = bn;
-      }
-    double d[8];
+    for (int q = 0; q < 8; ++q) {
+      const double bn = fma(u2, b1[q], T->cheb[j][q] - b2[q]);
+      b2[q] = b1[q];
+      b1[q] = bn;
+    }
+  double d[8];
 #pragma unroll
-    for (int q = 0; q < 8; ++q) d[q] = fma(u, b1[q], T->cheb[0][q] - b2[q]);
-    double sn, cs;
-    sincos(T->k.x * r, &sn, &cs);
-    const double e1 = exp(-T->k.y * r), a = sqrt(t), a1 = a * e1, a2 = a / e1;
-    const cplx p1 = cmul(cmk(T->sq1.x, T->sq1.y), cmk(a1 * cs, a1 * sn));
-    const cplx p2 = cmul(cmk(T->sq2.x, T->sq2.y), cmk(a2 * cs, -a2 * sn));
-    o.h0 = cadd(p1, cmul(p1, cmk(d[0], d[1])));
-    const cplx h1 = cadd(p1, cmul(p1, cmk(d[2], d[3])));
-    const cplx g0 = cadd(p2, cmul(p2, cmk(d[4], d[5])));
-    const cplx g1 = cadd(p2, cmul(p2, cmk(d[6], d[7])));
-    o.h1 = cmk(h1.y, -h1.x);                      // e^{-i pi/2}
-    o.j0 = cscale(cadd(o.h0, g0), 0.5);
-    o.j1 = cscale(cadd(o.h1, cmk(-g1.y, g1.x)), 0.5);  // e^{+i pi/2}
-  }
+  for (int q = 0; q < 8; ++q) d[q] = fma(u, b1[q], T->cheb[0][q] - b2[q]);
+  double sn, cs;
+  sincos(T->w.k.x * r, &sn, &cs);
+  const double e1 = exp(-T->w.k.y * r), a = sqrt(t), a1 = a * e1, a2 = a / e1;
+  const cplx p1 = cmul(cmk(T->sq1.x, T->sq1.y), cmk(a1 * cs, a1 * sn));
+  const cplx p2 = cmul(cmk(T->sq2.x, T->sq2.y), cmk(a2 * cs, -a2 * sn));
+  o.h0 = cadd(p1, cmul(p1, cmk(d[0], d[1])));
+  const cplx h1 = cadd(p1, cmul(p1, cmk(d[2], d[3])));
+  const cplx g0 = cadd(p2, cmul(p2, cmk(d[4], d[5])));
+  const cplx g1 = cadd(p2, cmul(p2, cmk(d[6], d[7])));
+  o.h1 = cmk(h1.y, -h1.x);                      // e^{-i pi/2}
+  o.j0 = cscale(cadd(o.h0, g0), 0.5);
+  o.j1 = cscale(cadd(o.h1, cmk(-g1.y, g1.x)), 0.5);  // e^{+i pi/2}
   return o;
 }
 
@@ -278,16 +252,86 @@ __device__ inline hk_dd dd_mul(hk_dd a, hk_dd b) {
   const double p = a.h * b.h;
   return dd_sum(p, fma(a.h, b.h, -p) + (a.h * b.l + a.l * b.h));
 }
-__device__ inline hk_dd dd_div(hk_dd a, double d) {  // d exact
-  const double q = a.h / d;
-  return dd_sum(q, (fma(-q, d, a.h) + a.l) / d);
-}
 struct hk_ddc {
   hk_dd x, y;
 };
 __device__ inline hk_ddc ddc_mul(hk_ddc a, hk_ddc b) {
   const hk_dd yy = dd_mul(a.y, b.y);
   return {dd_add(dd_mul(a.x, b.x), {-yy.h, -yy.l}), dd_add(dd_mul(a.x, b.y), dd_mul(a.y, b.x))};
+}
+
+// The factors of the series' coefficients, in the same precision: 1 / (m!)^2,
+// 1 / (m! (m + 1)!), and these times the harmonic sums H_m and H_m + H_{m+1} (at compile
+// time, where a product is split instead of fused).
+struct hk_fact_tab {
+  hk_dd r[HK_NS][4];
+};
+constexpr hk_dd ct_sum(double a, double b) {
+  const double s = a + b, t = s - a;
+  return {s, (a - (s - t)) + (b - t)};
+}
+constexpr hk_dd ct_prod(double a, double b) {
+  const double ca = 134217729.0 * a, ah = ca - (ca - a), al = a - ah;
+  const double cb = 134217729.0 * b, bh = cb - (cb - b), bl = b - bh;
+  const double p = a * b;
+  return {p, ((ah * bh - p) + ah * bl + al * bh) + al * bl};
+}
+constexpr hk_dd ct_add(hk_dd a, hk_dd b) {
+  const hk_dd s = ct_sum(a.h, b.h);
+  return ct_sum(s.h, s.l + (a.l + b.l));
+}
+constexpr hk_dd ct_mul(hk_dd a, hk_dd b) {
+  const hk_dd p = ct_prod(a.h, b.h);
+  return ct_sum(p.h, p.l + (a.h * b.l + a.l * b.h));
+}
+constexpr hk_dd ct_div(hk_dd a, double d) {  // d exact
+  const double q = a.h / d;
+  const hk_dd p = ct_prod(q, d);
+  return ct_sum(q, (((a.h - p.h) - p.l) + a.l) / d);
+}
+constexpr hk_fact_tab hk_fact_make() {
+  hk_fact_tab t{};
+  hk_dd f = {1.0, 0.0}, h = {0.0, 0.0};
+  for (int m = 0; m < HK_NS; ++m) {
+    if (m > 0) {
+      f = ct_div(f, (double)m * m);
+      h = ct_add(h, ct_div({1.0, 0.0}, m));
+    }
+    t.r[m][0] = f;
+    t.r[m][1] = ct_div(f, m + 1.0);
+    t.r[m][2] = ct_mul(f, h);
+    t.r[m][3] = ct_mul(t.r[m][1], ct_add(ct_add(h, h), ct_div({1.0, 0.0}, m + 1.0)));
+  }
+  return t;
+}
+__constant__ hk_fact_tab hk_fact = hk_fact_make();
+
+// Item i of the tables of wavenumber k: term i of the series, or, for i = HK_NS, the rest.
+__device__ inline void hk_wave_item(cplx k, int i, hk_wave *T) {
+  // 1 / P for P = 2^floor(log2 |k|)
+  const double ak = hypot(k.x, k.y), sc = __hiloint2double(0x7fe00000 - (__double2hiint(ak) & 0x7ff00000), 0);
+  if (i < HK_NS) {
+    // (-k^2 / 4 P^2)^i and its companions
+    const double x = k.x * sc, y = k.y * sc;  // k / P, exact
+    const hk_dd xx = dd_mul({x, 0.0}, {-0.25 * x, 0.0}), yy = dd_mul({y, 0.0}, {0.25 * y, 0.0});
+    hk_ddc f = {dd_add(xx, yy), dd_mul({x, 0.0}, {-0.5 * y, 0.0})}, c = {{1.0, 0.0}, {0.0, 0.0}};
+    for (int e = i; e > 0; e >>= 1) {
+      if (e & 1) c = ddc_mul(c, f);
+      f = ddc_mul(f, f);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const hk_dd a = hk_fact.r[i][q];
+      T->ser[i][2 * q] = dd_mul(c.x, a).h;
+      T->ser[i][2 * q + 1] = dd_mul(c.y, a).h;
+    }
+  } else {
+    T->ak = ak;
+    T->scale = 1.0 / sc;
+    T->th = atan2(k.y, k.x);
+    T->k = k;
+    T->ik = crecip(k);
+  }
 }
 
 // The tables of two wavenumbers, one workgroup each.
@@ -299,9 +343,7 @@ __global__ __launch_bounds__(HK_RAY_NT) void hankel_ray_kernel(cplx k0, cplx k1,
   const cplx k = blockIdx.x ? k1 : k0;
   hk_ray *T = out + blockIdx.x;
   const int tid = threadIdx.x;
-  // 1 / P for P = 2^floor(log2 |k|)
-  const double ak = hypot(k.x, k.y), sc = __hiloint2double(0x7fe00000 - (__double2hiint(ak) & 0x7ff00000), 0);
-  const double th = atan2(k.y, k.x), cth = k.x / ak, sth = k.y / ak;
+  const double ak = hypot(k.x, k.y), th = atan2(k.y, k.x), cth = k.x / ak, sth = k.y / ak;
   if (tid < 4 * M) C[tid] = cospi((double)tid / (2 * M));
   {
     // F_nu - 1 = int weight ((1 + i u / 2z)^{nu - 1/2} - 1) at node m, H^(1) (sg = 0) and,
@@ -337,39 +379,10 @@ __global__ __launch_bounds__(HK_RAY_NT) void hankel_ray_kernel(cplx k0, cplx k1,
     double s = 0.0;
     for (int m = 0; m < M; ++m) s = fma(D[q][m], C[(j * (2 * m + 1)) % (4 * M)], s);
     T->cheb[j][q] = s * ((j == 0) ? 1.0 : 2.0) / M;
-  } else if (tid >= 512 && tid < 512 + HK_NS) {
-    // (-k^2 / 4 P^2)^m / (m!)^2 and its companions
-    const int m = tid - 512;
-    const double x = k.x * sc, y = k.y * sc;  // k / P, exact
-    const hk_dd xx = dd_mul({x, 0.0}, {-0.25 * x, 0.0}), yy = dd_mul({y, 0.0}, {0.25 * y, 0.0});
-    hk_ddc f = {dd_add(xx, yy), dd_mul({x, 0.0}, {-0.5 * y, 0.0})}, c = {{1.0, 0.0}, {0.0, 0.0}};
-    for (int e = m; e > 0; e >>= 1) {
-      if (e & 1) c = ddc_mul(c, f);
-      f = ddc_mul(f, f);
-    }
-    hk_dd h = {0.0, 0.0};  // H_m
-    for (int i = 1; i <= m; ++i) {
-      c.x = dd_div(c.x, (double)i * i);
-      c.y = dd_div(c.y, (double)i * i);
-      h = dd_add(h, dd_div({1.0, 0.0}, i));
-    }
-    const hk_dd h1 = dd_add(h, dd_add(h, dd_div({1.0, 0.0}, m + 1.0)));  // H_m + H_{m+1}
-    const hk_ddc c1 = {dd_div(c.x, m + 1.0), dd_div(c.y, m + 1.0)};
-    T->ser[m][0] = c.x.h;
-    T->ser[m][1] = c.y.h;
-    T->ser[m][2] = c1.x.h;
-    T->ser[m][3] = c1.y.h;
-    T->ser[m][4] = dd_mul(c.x, h).h;
-    T->ser[m][5] = dd_mul(c.y, h).h;
-    T->ser[m][6] = dd_mul(c1.x, h1).h;
-    T->ser[m][7] = dd_mul(c1.y, h1).h;
+  } else if (tid >= 512 && tid <= 512 + HK_NS) {
+    hk_wave_item(k, tid - 512, &T->w);
   } else if (tid == 1023) {
     double sn, cs;
-    T->ak = ak;
-    T->scale = 1.0 / sc;
-    T->th = th;
-    T->k = k;
-    T->ik = crecip(k);
     const double c = sqrt(2.0 / BM_PI);
     sincos(-0.5 * th - 0.25 * BM_PI, &sn, &cs);
     T->sq1 = cmk(c * cs, c * sn);
