@@ -118,7 +118,9 @@ __global__ __launch_bounds__(256) void gemv_partial_kernel(int m, int k, int nr,
 // slice of B goes through LDS in operand order.  The steps of a slice of SK_KC are
 // loaded together, one slice ahead.  Solve with 32 right-hand sides, N = 4096: 994 us;
 // 1068 us with 32 rows per wavefront and slices of 16 (fewer wavefronts per SIMD),
-// 1028 us with 16 rows, slices of 16 and 1024 workgroups.
+// 1028 us with 16 rows, slices of 16 and 1024 workgroups.  A product takes 210 us there:
+// 2.6 TB/s of A (a large copy moves 5.1) and 41 TFLOP/s of 72, so neither bounds it alone;
+// a wavefront has one slice of A on its way and meets a barrier with every slice of B.
 #define SK_ROWS 64  // rows per workgroup
 #define SK_KC 32
 #define SK_WG 512
@@ -265,8 +267,8 @@ int bm_launch_gemv_sub(hipStream_t s, int m, int k, int nr, const cplx *A, int64
 // launch order, block by block, so a workgroup only waits for workgroups that started
 // before it.  (The groups are independent chains of the same length; one workgroup
 // that took 32 right-hand sides ran four products between the arrival of a block and
-// its publication: 815 us per solve at N = 4096, with a workgroup per group 239 us.)  The ticket
-// counters and both solves' block areas share one buffer that a single fill with
+// its publication: 815 us per solve at N = 4096, with a workgroup per group 239 us.)
+// The ticket counters and both solves' block areas share one buffer that a single fill with
 // the all-ones pattern prepares (a counter then starts at -1).  A solved block
 // is published to zbuf (pre-filled with an all-ones pattern) with agent-scope
 // stores, and every lane polls the words it uses as a matrix-core operand until
@@ -433,8 +435,8 @@ static int launch_trsv(hipStream_t s, bm_getrf_ws *w, int lower, int n, const T 
   cplx *zb = w->zbuf + 1 + (lower ? 0 : (size_t)nblk * TS_NB * BM_MAX_NRHS);
   const dim3 grid(nblk * ((nrhs + 7) / 8));
   if (lower)
-    hipLaunchKernelGGL((trsv_kernel<true, T>), grid, dim3(256), 0, s, n, LU, (long)ld, dinv, X, (long)ldx, nrhs, ticket,
-                       zb, dev_err);
+    hipLaunchKernelGGL((trsv_kernel<true, T>), grid, dim3(256), 0, s, n, LU, (long)ld, dinv, X, (long)ldx, nrhs,
+                       ticket, zb, dev_err);
   else
     hipLaunchKernelGGL((trsv_kernel<false, T>), grid, dim3(256), 0, s, n, LU, (long)ld, dinv, X, (long)ldx, nrhs, ticket,
                        zb, dev_err);
