@@ -192,7 +192,7 @@ __global__ __launch_bounds__(256, G2_OCC) void zgemm32_kernel(int m, int n, int 
 //
 // Large updates are bound by the traffic of C (read and written once: 3.3 TB/s at
 // R = 8064, where a large copy moves 5.1, with the matrix cores at 79 TFLOP/s of 157;
-// over a factorisation of order 8192 the counters show 1.04 times the bytes of C and
+// over a factorisation of order 8192 the counters show 1.08 times the bytes of C and
 // the matrix cores busy half of the cycles), small ones by one tile's chain of loads and
 // products.  A 64 x 64 tile has a quarter of that chain of the 128 x 128 tile of the
 // product above, and C comes in beside the last products instead of after them.
