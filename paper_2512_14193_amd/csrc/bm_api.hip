@@ -341,7 +341,6 @@ int bm_block_lu(bm_problem *p, int32_t *info) {
   // form's side streams wait for each other as well, and a capture in which streams had
   // joined through each other ended the process.
   if (p->form == BM_MIXED && p->prec == BM_PREC_FP64 && p->pipeline && !is_captured(p->stream)) {
-    if (int rc0 = bm_getrf_pipe_create(p->gws)) return rc0;
     // Theorem thm:LU: U33 = -M31 M13 - M32 M23 = -[M31 M32] [M13; M23], formed in
     // column segments beside the factorisation of the columns already formed
     phase_begin(p, BM_PH_LU);

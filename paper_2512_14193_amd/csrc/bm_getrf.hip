@@ -1209,9 +1209,10 @@ static void pipe_destroy(bm_lu_pipe *q) {
   delete q;
 }
 
-int bm_getrf_pipe_create(bm_getrf_ws *w) {
-  if (!w || !w->side) return BM_E_ARG;
+// the streams and events of the overlap, made by the first factorisation that takes it
+static int pipe_create(bm_getrf_ws *w) {
   if (w->pipe) return BM_OK;
+  if (!w->side) return BM_E_ARG;
   bm_lu_pipe *q = new (std::nothrow) bm_lu_pipe();
   if (!q) return BM_E_NOMEM;
   memset((void *)q, 0, sizeof(*q));
@@ -1242,11 +1243,10 @@ size_t bm_getrf_pipe_w_elems(int n) {
 int bm_getrf_schur_run(hipStream_t s, int n, cplx alpha, const cplx *bot, int64_t ldbot, const cplx *top,
                        int64_t ldtop, int k, cplx *A, int64_t lda, int32_t *ipiv, int32_t *dev_err, bm_getrf_ws *w,
                        cplx *W, size_t w_elems, int *nseg_out) {
-  if (!w || w->n < n || n < 1 || n > BM_PIPE_MAX_N || !w->aux || !w->pipe || k < 1 || !W || !nseg_out ||
+  if (!w || w->n < n || n < 1 || n > BM_PIPE_MAX_N || !w->aux || k < 1 || !W || !nseg_out ||
       w_elems < bm_getrf_pipe_w_elems(n))
     return BM_E_ARG;
   *nseg_out = 0;
-  bm_lu_pipe *q = w->pipe;
   lu_shape shape[SP_MAXB];
   int ncu = 0;
   if (int rc0 = lu_begin(s, n, dev_err, w, shape, &ncu)) return rc0;
@@ -1269,6 +1269,8 @@ int bm_getrf_schur_run(hipStream_t s, int n, cplx alpha, const cplx *bot, int64_
     if (ps) bm_phase_end_on(ps, BM_PH_SCHUR, s);
     return bm_getrf_run(s, n, A, lda, ipiv, dev_err, w, 0);
   }
+  if (int rc0 = pipe_create(w)) return rc0;  // (an order without a plan needs none)
+  bm_lu_pipe *q = w->pipe;
   *nseg_out = nseg;
   const long ldal = (long)lda;
   auto cols = [&](int i, int *c0, int *c1) {

@@ -344,7 +344,6 @@ size_t bm_getrf_ws_bytes(int n);  // device bytes bm_getrf_ws_create(n) allocate
 // W: split-K workspace of bm_getrf_pipe_w_elems(n) complex values
 #define BM_PIPE_MAX_N 4096
 size_t bm_getrf_pipe_w_elems(int n);
-int bm_getrf_pipe_create(bm_getrf_ws *w);  // the extra streams and events (once)
 // (*nseg: the segments used, 0 when the model chose to form the product first)
 int bm_getrf_schur_run(hipStream_t s, int n, cplx alpha, const cplx *bot, int64_t ldbot, const cplx *top,
                        int64_t ldtop, int k, cplx *A, int64_t lda, int32_t *ipiv, int32_t *dev_err, bm_getrf_ws *w,
